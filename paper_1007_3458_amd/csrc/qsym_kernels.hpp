@@ -440,6 +440,32 @@ __device__ __forceinline__ void pair32(const double4 &pj, double xi, double yi, 
     az = fma(ms, dz, az);
 }
 
+// the seed of r^2 in the pair terms (the test of split_large's bodies takes
+// the same r^2, so that it and the pair loop's are complements)
+template <int PREC>
+__device__ __forceinline__ double r2_seed(const KickArgs &ka)
+{
+    return PREC == 0 ? ka.r2seed : 1e-24;
+}
+
+// Bodies of a 64-body sub-tile whose Hill term stands far above the rest
+// (a planet, a nearly parabolic orbit): they are left out of the tile's
+// maxima, which they would raise for every other pair, and their pairs take
+// a test of their own after the pair loop.  Returns the lanes (none when more
+// than four stand out: then the maxima cover them all), and clears their
+// terms.  Eight times the smallest term: a disk's own bodies lie within three
+// of each other.
+template <int MODE>
+__device__ __forceinline__ unsigned long long split_large(bool ok, double &ch, double &A, double &cv)
+{
+    const double w = MODE == 1 ? ch * A : ch;
+    const double least = -wave_max(ok ? -w : -__builtin_inf());
+    unsigned long long m = __ballot(ok && w > 8.0 * least);
+    if (__popcll(m) > 4) m = 0ull;
+    if ((m >> (threadIdx.x & 63)) & 1ull) ch = A = cv = 0.0;
+    return m;
+}
+
 // padding of a partial j-tile: far away (r^2 ~ 3e36, finite in FP32) and massless, so it
 // adds nothing and never passes the crude bound
 constexpr double kFar = 1e18;
@@ -448,9 +474,49 @@ constexpr double kFar = 1e18;
 // and given the exact test after the tile, so the pair loop has no call
 constexpr int kCrudeQ = 512;
 
+// upper bound of the squared crude limit of two bodies with these terms (the
+// factor covers the different rounding of r^2)
+template <int MODE>
+__device__ __forceinline__ double pair_bound(const KickArgs &ka, double hi, double Ai, double vi,
+                                             double hj, double Aj, double vj)
+{
+    const double Rb = MODE == 1 ? ka.aE * (hi + hj) * (Ai + Aj) / 2.0 : ka.aE * (hi + hj);
+    const double th = ka.cs * (Rb + ka.tau_abs * (vi + vj));
+    return th * th * 1.000000000001;
+}
+
+// A tile whose hits overflowed the queue (a crowd).  A thread takes its body i at (xi, yi, zi) against the tile's
+// nj bodies from jt on again, with the pair's own threshold in place of the
+// tile's: the j side from LDS (pos(jj) and the crude terms cj, read by all
+// lanes at once), so a pair costs some 15 instructions; the few that pass
+// take the exact test.  (That test on every pair, each operand from global
+// memory, was one chain of a tile's dependent reads a thread; with the
+// planets in the tile's maxima it set the crude kick's time for small
+// systems.  Measured at 104 / 1024 / 4100 bodies: 46.7 / 57.0 / 59.5 us, with
+// split_large and this pass 19.1 / 21.6 / 30.1 us.)
+template <int BS, int MODE, class Pos>
+__device__ __forceinline__ void tile_exact(const KickArgs &ka, int i, double xi, double yi,
+                                           double zi, int jt, int nj, const double (*cj)[BS],
+                                           Pos pos)
+{
+    const Dev &d = ka.d;
+    const double hi = d.ch[i], Ai = d.A[i], vi = d.cv[i];
+#pragma unroll 4
+    for (int jj = 0; jj < nj; ++jj) {
+        double xj, yj, zj;
+        pos(jj, xj, yj, zj);
+        const double dx = xj - xi, dy = yj - yi, dz = zj - zi;
+        const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+        if (r2 < pair_bound<MODE>(ka, hi, Ai, vi, cj[0][jj], cj[1][jj], cj[2][jj]))
+            crude_exact(ka, i, jt + jj);
+    }
+}
+
 template <int BS, int IPL, int MODE>
 __device__ __forceinline__ void crude_drain(const KickArgs &ka, int i0, int ni, int jt, int jend,
-                                            const int *ii, unsigned *qbuf, unsigned *qn)
+                                            const double *xi, const double *yi, const double *zi,
+                                            const double4 *sj, const double (*cj)[BS],
+                                            unsigned *qbuf, unsigned *qn)
 {
     const unsigned n = *qn;
     const int tid = threadIdx.x;
@@ -461,12 +527,18 @@ __device__ __forceinline__ void crude_drain(const KickArgs &ka, int i0, int ni, 
             if (lt + u * BS < ni) crude_exact(ka, i0 + lt + u * BS, jt + jj);
         }
     } else {
-        // queue overflow (a dense tile): exact test of every pair of the tile
-        const int je = min(jt + BS, jend);
+        // queue overflow: the tile is still in LDS
+        const int nj = min(BS, jend - jt);
 #pragma unroll
         for (int u = 0; u < IPL; ++u)
             if (tid + u * BS < ni)
-                for (int j = jt; j < je; ++j) crude_exact(ka, ii[u], j);
+                tile_exact<BS, MODE>(ka, i0 + tid + u * BS, xi[u], yi[u], zi[u], jt, nj, cj,
+                                     [&](int jj, double &x, double &y, double &z) {
+                                         const double4 p = sj[jj];
+                                         x = p.x;
+                                         y = p.y;
+                                         z = p.z;
+                                     });
     }
 }
 
@@ -486,11 +558,12 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
     __shared__ double smax[3][NW];
     __shared__ unsigned qbuf[MODE ? kCrudeQ : 1];
     __shared__ unsigned qn;
+    __shared__ double scj[MODE ? 3 : 1][BS];   // the tile's crude terms
+    __shared__ unsigned long long slarge[NW];  // its bodies left out of the maxima
 
     double xi[IPL], yi[IPL], zi[IPL];
     double ax[IPL], ay[IPL], az[IPL];
     double hi[IPL], Ai[IPL], vi[IPL];
-    int ii[IPL];
 #pragma unroll
     for (int u = 0; u < IPL; ++u) {
         const int i = it.i0 + tid + u * BS;
@@ -504,7 +577,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
             Ai[u] = ok ? d.A[i] : 0.0;
             vi[u] = ok ? d.cv[i] : 0.0;
         }
-        ii[u] = ok ? i : 0x7fffffff;
     }
     if (MODE && tid == 0) qn = 0u;
     const int jend = it.j0 + it.nj;
@@ -517,7 +589,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
         __syncthreads();
         if constexpr (MODE != 0) {
             if (qtile >= 0) {
-                if (qn) crude_drain<BS, IPL, MODE>(ka, it.i0, it.ni, qtile, it.j0 + it.nj, ii, qbuf, &qn);
+                if (qn)
+                    crude_drain<BS, IPL, MODE>(ka, it.i0, it.ni, qtile, jend, xi, yi, zi, sj, scj,
+                                               qbuf, &qn);
                 __syncthreads();
                 if (tid == 0) qn = 0u;
                 qtile = -1;
@@ -533,10 +607,15 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
         if (MODE && pred) {
             // tile maxima of the crude-sweep terms (all non-negative)
             double t0 = okj ? d.ch[j] : 0.0, t1 = okj ? d.A[j] : 0.0, t2 = okj ? d.cv[j] : 0.0;
+            scj[0][tid] = t0;
+            scj[1][tid] = t1;
+            scj[2][tid] = t2;
+            const unsigned long long m = split_large<MODE>(okj, t0, t1, t2);
             t0 = wave_max(t0);
             t1 = wave_max(t1);
             t2 = wave_max(t2);
             if ((tid & 63) == 0) {
+                slarge[tid >> 6] = m;
                 smax[0][tid >> 6] = t0;
                 smax[1][tid >> 6] = t1;
                 smax[2][tid >> 6] = t2;
@@ -567,23 +646,51 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
                     const double th = ka.cs * (Rb + ka.tau_abs * (vi[u] + VT));
                     th2[u] = th * th * 1.000000000001;
                 }
-#pragma unroll 4
-                for (int jj = 0; jj < ntj; ++jj) {
-                    const double4 pj = sj[jj];
+                // four j at a time with one branch for all their hits: a
+                // branch per pair kept the four pairs' chains apart (the
+                // crude kick 19.1 -> 13.9 us at 104 bodies, 21.6 -> 16.2 at 1024)
+                for (int j4 = 0; j4 < ntj; j4 += 4) {
+                    unsigned hits = 0u;
 #pragma unroll
-                    for (int u = 0; u < IPL; ++u) {
-                        double r2;
-                        if constexpr (PREC == 0)
-                            pair64(pj, xi[u], yi[u], zi[u], seed, c158, c32, ax[u], ay[u], az[u], r2);
-                        else
-                            pair32(pj, xi[u], yi[u], zi[u], ax[u], ay[u], az[u], r2);
-                        if (r2 < th2[u]) {
-                            const unsigned k = atomicAdd(&qn, 1u);
-                            if (k < (unsigned)kCrudeQ)
-                                qbuf[k] = ((unsigned)tid << 16) | ((unsigned)u << 8) | (unsigned)jj;
+                    for (int q = 0; q < 4; ++q) {
+                        const double4 pj = sj[j4 + q];
+#pragma unroll
+                        for (int u = 0; u < IPL; ++u) {
+                            double r2;
+                            if constexpr (PREC == 0)
+                                pair64(pj, xi[u], yi[u], zi[u], seed, c158, c32, ax[u], ay[u], az[u], r2);
+                            else
+                                pair32(pj, xi[u], yi[u], zi[u], ax[u], ay[u], az[u], r2);
+                            hits |= r2 < th2[u] ? 1u << (q * IPL + u) : 0u;
                         }
                     }
+                    for (; hits; hits &= hits - 1) {
+                        const int h = __builtin_ctz(hits), q = h / IPL, u = h % IPL;
+                        const unsigned k = atomicAdd(&qn, 1u);
+                        if (k < (unsigned)kCrudeQ)
+                            qbuf[k] = ((unsigned)tid << 16) | ((unsigned)u << 8) | (unsigned)(j4 + q);
+                    }
                 }
+                // the bodies left out of the maxima: the pairs that lie
+                // outside the tile's bound (the others are queued above) and
+                // inside their own
+                for (int w = 0; w < NW; ++w)
+                    for (unsigned long long m = slarge[w]; m; m &= m - 1) {
+                        const int jj = 64 * w + __builtin_ctzll(m);
+                        const double4 pj = sj[jj];
+#pragma unroll
+                        for (int u = 0; u < IPL; ++u) {
+                            const double dx = pj.x - xi[u], dy = pj.y - yi[u], dz = pj.z - zi[u];
+                            const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, r2_seed<PREC>(ka))));
+                            if (!(r2 < th2[u]) &&
+                                r2 < pair_bound<MODE>(ka, hi[u], Ai[u], vi[u], scj[0][jj], scj[1][jj],
+                                                      scj[2][jj])) {
+                                const unsigned k = atomicAdd(&qn, 1u);
+                                if (k < (unsigned)kCrudeQ)
+                                    qbuf[k] = ((unsigned)tid << 16) | ((unsigned)u << 8) | (unsigned)jj;
+                            }
+                        }
+                    }
                 qtile = jt;
                 continue;
             }
@@ -613,7 +720,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
     if constexpr (MODE != 0) {
         __syncthreads();
         if (qtile >= 0 && qn)
-            crude_drain<BS, IPL, MODE>(ka, it.i0, it.ni, qtile, it.j0 + it.nj, ii, qbuf, &qn);
+            crude_drain<BS, IPL, MODE>(ka, it.i0, it.ni, qtile, jend, xi, yi, zi, sj, scj, qbuf,
+                                       &qn);
     }
     const int s = it.sys;
     const int ns = d.sys_off[s + 1] - d.sys_off[s];
@@ -819,18 +927,6 @@ __device__ void sym_flush(const KickArgs &ka, const int *qi, const int *qj, unsi
     }
 }
 
-// a tile whose hits overflowed the queue: the exact test of every pair of
-// the tile with j > i (appended one by one; rare)
-template <int BS, int IPL>
-__device__ void sym_tile_exact(const KickArgs &ka, int jt, int jend, const int *iu, const bool *oku)
-{
-    const int je = min(jt + BS, jend);
-#pragma unroll
-    for (int u = 0; u < IPL; ++u)
-        if (oku[u])
-            for (int j = jt; j < je; ++j) crude_exact(ka, iu[u], j);
-}
-
 // REC: the variant that writes workgroup records (profiling with records;
 // a separate instantiation, so the kernel timed otherwise carries no trace
 // of them: any extra live value changes this kernel's register
@@ -872,6 +968,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
     // passing the exact test before their one append
     __shared__ int qi[MODE ? kCrudeQ : 1], qj[MODE ? kCrudeQ : 1];
     __shared__ int2 cl[MODE ? kCrudeQ : 1];
+    __shared__ unsigned long long slarge[MODE ? NW : 1];   // bodies left out of the tile's maxima
     __shared__ unsigned qn, cn;
     __shared__ int cbase;
 
@@ -951,10 +1048,12 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
             }
             if constexpr (MODE != 0) {
                 double t0 = okj ? d.ch[j] : 0.0, t1 = okj ? d.A[j] : 0.0, t2 = okj ? d.cv[j] : 0.0;
+                const unsigned long long m = split_large<MODE>(okj, t0, t1, t2);
                 t0 = wave_max(t0);
                 t1 = wave_max(t1);
                 t2 = wave_max(t2);
                 if (lane == 0) {
+                    slarge[wv] = m;
                     smax[0][wv] = t0;
                     smax[1][wv] = t1;
                     smax[2][wv] = t2;
@@ -1008,6 +1107,33 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 wpart[wv][1][64 * sub + lane] = fy;
                 wpart[wv][2][64 * sub + lane] = fz;
             }
+            if constexpr (MODE != 0) {
+                // the bodies left out of the maxima: the pairs that lie
+                // outside the tile's bound (the others are queued above) and
+                // inside their own
+                for (int w2 = 0; w2 < NW; ++w2)
+                    for (unsigned long long m = slarge[w2]; m; m &= m - 1) {
+                        const int jj = __builtin_ctzll(m), jl = jt + 64 * w2 + jj;
+                        const double2 pxy = txy[w2][jj];
+                        const double zj = tzm[w2][jj].x;
+                        const double hj = d.ch[jl], Aj = d.A[jl], vj = d.cv[jl];
+#pragma unroll
+                        for (int u = 0; u < IPL; ++u) {
+                            const int i = iu[u];
+                            if (!oku[u] || jl <= i) continue;
+                            const double dx = pxy.x - xi[u], dy = pxy.y - yi[u], dz = zj - zi[u];
+                            const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, r2_seed<PREC>(ka))));
+                            if (!(r2 < th2[u]) &&
+                                r2 < pair_bound<MODE>(ka, hi[u], Ai[u], vi[u], hj, Aj, vj)) {
+                                const unsigned q = atomicAdd(&qn, 1u);
+                                if (q < (unsigned)kCrudeQ) {
+                                    qi[q] = i;
+                                    qj[q] = jl;
+                                }
+                            }
+                        }
+                    }
+            }
             __syncthreads();
             // the tile's reactions, waves in order, onto the slot
             if (okj) {
@@ -1025,7 +1151,24 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 unsigned keep = nq;
                 if (nq > (unsigned)kCrudeQ) {
                     // this tile's pushes overflowed: drop them, test the tile
-                    sym_tile_exact<BS, IPL>(ka, jt, jend, iu, oku);
+                    // (its crude terms go where the reactions were; nq is
+                    // uniform, so the whole workgroup takes the barriers)
+                    __syncthreads();
+                    wpart[0][0][tid] = okj ? d.ch[j] : 0.0;
+                    wpart[0][1][tid] = okj ? d.A[j] : 0.0;
+                    wpart[0][2][tid] = okj ? d.cv[j] : 0.0;
+                    __syncthreads();
+#pragma unroll
+                    for (int u = 0; u < IPL; ++u)
+                        if (oku[u])
+                            tile_exact<BS, MODE>(
+                                ka, iu[u], xi[u], yi[u], zi[u], jt, min(BS, jend - jt),
+                                wpart[0], [&](int jj, double &x, double &y, double &z) {
+                                    const double2 a2 = txy[jj >> 6][jj & 63];
+                                    x = a2.x;
+                                    y = a2.y;
+                                    z = tzm[jj >> 6][jj & 63].x;
+                                });
                     keep = qstart;
                 }
                 const bool last = ib + BI >= it.i0 + it.ni && jt + BS >= jend;

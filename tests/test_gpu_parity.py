@@ -107,6 +107,49 @@ def test_crude_candidates_match(Q, orc, name, shape):
     ctx.close()
 
 
+def _planets_among(n, at, seed, m=1e-8):
+    """A disk of n bodies whose four planets stand at body indices ``at``."""
+    s = inputs.make_disk(f"among{n}", seed, n - 4, m, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025)
+    rest = iter(range(4, n))
+    where = dict(zip(at, range(4)))
+    return s.permuted(np.array([where[i] if i in where else next(rest) for i in range(n)]))
+
+
+@pytest.mark.parametrize("n,at", [(5, (0, 1, 2, 4)), (64, (0, 63, 1, 62)), (65, (64, 0, 1, 63)),
+                                  (129, (128, 0, 64, 127)), (300, (298, 299, 297, 296)),
+                                  (700, (0, 255, 256, 699))])
+@pytest.mark.parametrize("hill_mode", [0, 1])
+def test_crude_candidates_with_planets_anywhere(Q, orc, n, at, hill_mode):
+    """Bodies left out of a tile's crude bound (planets, one nearly parabolic
+    orbit) at the edges of tiles, and tiles with too many of them (massless
+    bodies beside massive ones): the candidate set of every kick form is the
+    oracle's."""
+    for kind in ("planets", "parabolic", "massless"):
+        s = _planets_among(n, at, 11 + n)
+        if kind == "parabolic" and n > 5:
+            r = np.linalg.norm(s.q[3])
+            s.v[3] *= np.sqrt(2.0 / r) * (1.0 - 1e-9) / np.linalg.norm(s.v[3])
+        if kind == "massless":
+            s.m[::3] = 0.0
+            s.h = np.cbrt(s.m / 3.0)
+        p = orc.make_params(hill_mode=hill_mode)
+        A, ve = orc.prepass(1.0, s.q, s.v)
+        ref = {tuple(x) for x in orc.crude(p, 0.05, s.q, s.h, A, ve)}
+        for sh in (dict(ipl=1, block=128, jchunk=128, remap=0, sym=0),
+                   dict(ipl=4, block=128, jchunk=256, remap=0, sym=0),
+                   dict(ipl=1, block=128, jchunk=128, remap=0, sym=1),
+                   dict(ipl=2, block=128, jchunk=512, remap=3, sym=1),
+                   dict(ipl=2, block=256, jchunk=512, remap=0, sym=2)):
+            say("crude candidates", n, at, hill_mode, kind, sh)
+            ctx = Q.Context(s, hill_mode=hill_mode)
+            ctx.set_kick_shape(**sh)
+            ctx.apply_kick(0.0, crude_tau=0.05)
+            c = ctx.candidates(cap=ctx.n * (ctx.n - 1) // 2 + 1)
+            assert len(c) == len({tuple(x) for x in c})
+            assert {tuple(x) for x in c} == ref
+            ctx.close()
+
+
 def test_drift_parity(Q, orc):
     s = crowded(300, 4)
     say("drift parity")
