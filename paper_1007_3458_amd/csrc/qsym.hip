@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "qsym_kernels.hpp"
@@ -761,26 +762,24 @@ hipError_t launch_kick_bs(qsym_ctx *c, int mode, int prec, hipStream_t st)
     if (c->shape[w].sym) {
         // one or two i per lane (the shape check admits no other)
         if constexpr (IPL <= 2) {
-            if (ka.rec) {
+            auto launch = [&](auto unit, auto recv) {
+                constexpr bool U = decltype(unit)::value, R = decltype(recv)::value;
                 if (prec == 0) {
-                    if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 0, true>), g, b, 0, st, ka);
-                    else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 0, true>), g, b, 0, st, ka);
-                    else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 0, true>), g, b, 0, st, ka);
+                    if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 0, U, R>), g, b, 0, st, ka);
+                    else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 0, U, R>), g, b, 0, st, ka);
+                    else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 0, U, R>), g, b, 0, st, ka);
                 } else {
-                    if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 1, true>), g, b, 0, st, ka);
-                    else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 1, true>), g, b, 0, st, ka);
-                    else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 1, true>), g, b, 0, st, ka);
+                    if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 1, U, R>), g, b, 0, st, ka);
+                    else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 1, U, R>), g, b, 0, st, ka);
+                    else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 1, U, R>), g, b, 0, st, ka);
                 }
-                return hipGetLastError();
-            }
-            if (prec == 0) {
-                if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 0>), g, b, 0, st, ka);
-                else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 0>), g, b, 0, st, ka);
-                else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 0>), g, b, 0, st, ka);
+            };
+            if (c->nsys == 1) {
+                if (ka.rec) launch(std::true_type{}, std::true_type{});
+                else launch(std::true_type{}, std::false_type{});
             } else {
-                if (mode == 0) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 0, 1>), g, b, 0, st, ka);
-                else if (mode == 1) hipLaunchKernelGGL((k_kick_sym<BS, IPL, 1, 1>), g, b, 0, st, ka);
-                else hipLaunchKernelGGL((k_kick_sym<BS, IPL, 2, 1>), g, b, 0, st, ka);
+                if (ka.rec) launch(std::false_type{}, std::true_type{});
+                else launch(std::false_type{}, std::false_type{});
             }
             return hipGetLastError();
         }
@@ -816,21 +815,20 @@ hipError_t launch_kick(qsym_ctx *c, int mode, hipStream_t st)
 }
 
 // resident workgroups per compute unit of the kick kernel a shape launches
-template <int BS, int IPL>
+template <int BS, int IPL, bool U>
 int occ_bs(int mode, int prec)
 {
     int occ = 0;
     hipError_t e = hipErrorInvalidValue;
-    if constexpr (IPL <= 2) {
-        if (prec == 0) {
-            if (mode == 0) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 0, 0>, BS, 0);
-            else if (mode == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 1, 0>, BS, 0);
-            else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 2, 0>, BS, 0);
-        } else {
-            if (mode == 0) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 0, 1>, BS, 0);
-            else if (mode == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 1, 1>, BS, 0);
-            else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_kick_sym<BS, IPL, 2, 1>, BS, 0);
-        }
+    auto query = [&](auto kernel) { e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, BS, 0); };
+    if (prec == 0) {
+        if (mode == 0) query(k_kick_sym<BS, IPL, 0, 0, U>);
+        else if (mode == 1) query(k_kick_sym<BS, IPL, 1, 0, U>);
+        else query(k_kick_sym<BS, IPL, 2, 0, U>);
+    } else {
+        if (mode == 0) query(k_kick_sym<BS, IPL, 0, 1, U>);
+        else if (mode == 1) query(k_kick_sym<BS, IPL, 1, 1, U>);
+        else query(k_kick_sym<BS, IPL, 2, 1, U>);
     }
     return (e == hipSuccess && occ > 0) ? occ : 1;
 }
@@ -838,8 +836,13 @@ int occ_bs(int mode, int prec)
 int kick_occupancy(qsym_ctx *c, int which, const Shape &sh)
 {
     const int mode = which ? 1 + c->p.hill_mode : 0;
-    if (sh.block == 256) return sh.ipl == 1 ? occ_bs<256, 1>(mode, c->p.precision) : occ_bs<256, 2>(mode, c->p.precision);
-    return sh.ipl == 1 ? occ_bs<128, 1>(mode, c->p.precision) : occ_bs<128, 2>(mode, c->p.precision);
+    auto occ = [&](auto unit) {
+        constexpr bool U = decltype(unit)::value;
+        const int prec = c->p.precision;
+        if (sh.block == 256) return sh.ipl == 1 ? occ_bs<256, 1, U>(mode, prec) : occ_bs<256, 2, U>(mode, prec);
+        return sh.ipl == 1 ? occ_bs<128, 1, U>(mode, prec) : occ_bs<128, 2, U>(mode, prec);
+    };
+    return c->nsys == 1 ? occ(std::true_type{}) : occ(std::false_type{});
 }
 
 int nblocks_chunks(qsym_ctx *c) { return (int)c->T.bchunk.size(); }

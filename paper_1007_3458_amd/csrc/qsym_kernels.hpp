@@ -6,6 +6,8 @@
 // sums), and the decision paths (per-body semi-major axis, fine encounter
 // test, r_crit) use plain IEEE +, -, *, /, sqrt in a fixed order.
 #pragma once
+#include <type_traits>
+
 #include "qsym_common.hpp"
 #include "qsym_kepler.hpp"
 
@@ -769,9 +771,12 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
 __device__ __forceinline__ double lane_rotate1(double v) { return dpp_f64<0x134>(v); }
 
 // FP64 pair of the symmetric kick: force on i into (ax, ay, az), reaction
-// on j into (fx, fy, fz); keep = false drops the pair
-__device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, double gmj, double xi,
-                                           double yi, double zi, double gmi, double seed,
+// on j into (fx, fy, fz), both in units of the system's reference mass (wj,
+// wi: the masses in that unit); keep = false drops the pair.  UNI: both
+// masses are the reference mass, so the two products with them fall away.
+template <bool UNI>
+__device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, double wj, double xi,
+                                           double yi, double zi, double wi, double seed,
                                            double c158, double c32, bool keep, double &ax,
                                            double &ay, double &az, double &fx, double &fy,
                                            double &fz, double &r2)
@@ -784,19 +789,20 @@ __device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, doub
     const double w = fma(e, fma(e, c158, c32), 1.0);
     double r3 = (y2 * y0) * w;
     if (!keep) r3 = 0.0;
-    const double msj = gmj * r3, msi = gmi * r3;
-    ax = fma(msj, dx, ax);
-    ay = fma(msj, dy, ay);
-    az = fma(msj, dz, az);
-    fx = fma(-msi, dx, fx);
-    fy = fma(-msi, dy, fy);
-    fz = fma(-msi, dz, fz);
+    const double sj = UNI ? r3 : wj * r3, si = UNI ? r3 : wi * r3;
+    ax = fma(sj, dx, ax);
+    ay = fma(sj, dy, ay);
+    az = fma(sj, dz, az);
+    fx = fma(-si, dx, fx);
+    fy = fma(-si, dy, fy);
+    fz = fma(-si, dz, fz);
 }
 
 // FP32 form: r^-3 from the FP32 rsq on the FP64 r^2, widened once and
-// multiplied by the FP64 G m of either body (as pair32)
-__device__ __forceinline__ void pair_sym32(double xj, double yj, double zj, double gmj, double xi,
-                                           double yi, double zi, double gmi, bool keep, double &ax,
+// multiplied by the FP64 mass of either body (as pair32)
+template <bool UNI>
+__device__ __forceinline__ void pair_sym32(double xj, double yj, double zj, double wj, double xi,
+                                           double yi, double zi, double wi, bool keep, double &ax,
                                            double &ay, double &az, double &fx, double &fy,
                                            double &fz, double &r2)
 {
@@ -804,30 +810,28 @@ __device__ __forceinline__ void pair_sym32(double xj, double yj, double zj, doub
     r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, 1e-24)));
     const float y = __builtin_amdgcn_rsqf((float)r2);
     const double r3 = keep ? (double)(y * y * y) : 0.0;
-    const double msj = gmj * r3, msi = gmi * r3;
-    ax = fma(msj, dx, ax);
-    ay = fma(msj, dy, ay);
-    az = fma(msj, dz, az);
-    fx = fma(-msi, dx, fx);
-    fy = fma(-msi, dy, fy);
-    fz = fma(-msi, dz, fz);
+    const double sj = UNI ? r3 : wj * r3, si = UNI ? r3 : wi * r3;
+    ax = fma(sj, dx, ax);
+    ay = fma(sj, dy, ay);
+    az = fma(sj, dz, az);
+    fx = fma(-si, dx, fx);
+    fy = fma(-si, dy, fy);
+    fz = fma(-si, dz, fz);
 }
 
-// How one lane group of 64 i meets a sub-tile of 64 j: all pairs (the
-// sub-tile lies past the group), the pairs l < (l + k) mod 64 (the sub-tile
-// is the group itself), or none (the sub-tile lies before it).
-enum { SYM_FULL = 0, SYM_DIAG = 1, SYM_SKIP = 2 };
-
-// 64 rotation steps of one wave over one sub-tile; lane group u (i_u =
-// u-th i of the lane) meets it as M0 (u = 0) / M1 (u = 1).  sxy, szm
-// point at the doubled sub-tile ((x, y) and (z, G m) rows of 128).
+// 64 rotation steps of one wave over one sub-tile.  DG says how the lane
+// groups of 64 i (group u: u-th i of the lane) meet the 64 j: -1, the
+// sub-tile lies past all of them (all pairs); else it is group DG itself,
+// which keeps the pairs l < (l + k) mod 64, the groups before it meet it
+// whole and those after it not at all.  UNI: see pair_sym64.  sxy, szm
+// point at the doubled sub-tile ((x, y) and (z, mass) rows of 128).
 // Crude-sweep hits are queued as body pairs (ib + lt, jsub + j offset) in
 // qi, qj.
-template <int MODE, int PREC, int IPL, int M0, int M1>
+template <int MODE, int PREC, int IPL, int DG, bool UNI>
 __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *szm, int lane,
                                             const double *xi, const double *yi,
-                                            const double *zi, const double *gmi,
-                                            const double *th2, const int *lt,
+                                            const double *zi, const double *wi,
+                                            const double *th2, int lt0,
                                             double seed, double c158, double c32, double *ax,
                                             double *ay, double *az, double &fx, double &fy,
                                             double &fz, int *qi, int *qj, unsigned *qn, int ib,
@@ -836,6 +840,7 @@ __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *s
     // the crude test's queue pushes split the loop body into blocks, and a
     // deep unroll then keeps too many values live: unroll less with it
     constexpr int UNR = MODE != 0 ? 2 : 8;
+    constexpr int NU = DG < 0 ? IPL : DG + 1;   // lane groups with pairs
     // with the crude test each rotation step is a block of its own (its
     // branch), so the crude kicks read the next step's j while this one
     // runs (a scheduling barrier keeps the reads there; entry lane + 64
@@ -844,47 +849,44 @@ __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *s
     double2 nxy = sxy[lane], nzm = szm[lane];
 #pragma unroll UNR
     for (int k = 0; k < 64; ++k) {
-        double xj, yj, zj, gmj;
+        double xj, yj, zj, wj;
         if constexpr (MODE != 0) {
-            xj = nxy.x; yj = nxy.y; zj = nzm.x; gmj = nzm.y;
+            xj = nxy.x; yj = nxy.y; zj = nzm.x; wj = nzm.y;
             nxy = sxy[lane + k + 1];
             nzm = szm[lane + k + 1];
             __builtin_amdgcn_sched_barrier(0);
         } else {
             const double2 pxy = sxy[lane + k], pzm = szm[lane + k];
-            xj = pxy.x; yj = pxy.y; zj = pzm.x; gmj = pzm.y;
+            xj = pxy.x; yj = pxy.y; zj = pzm.x; wj = pzm.y;
         }
         bool hit[IPL];
 #pragma unroll
-        for (int u = 0; u < IPL; ++u) {
-            const int M = u == 0 ? M0 : M1;
-            hit[u] = false;
-            if (M == SYM_SKIP) continue;
-            const bool keep = M == SYM_DIAG ? (k > 0 && lane + k < 64) : true;
+        for (int u = 0; u < NU; ++u) {
+            const bool keep = u == DG ? (k > 0 && lane + k < 64) : true;
             double r2;
             if constexpr (PREC == 0)
-                pair_sym64(xj, yj, zj, gmj, xi[u], yi[u], zi[u], gmi[u], seed, c158, c32, keep,
-                           ax[u], ay[u], az[u], fx, fy, fz, r2);
+                pair_sym64<UNI>(xj, yj, zj, wj, xi[u], yi[u], zi[u], wi[u], seed, c158, c32, keep,
+                                ax[u], ay[u], az[u], fx, fy, fz, r2);
             else
-                pair_sym32(xj, yj, zj, gmj, xi[u], yi[u], zi[u], gmi[u], keep, ax[u], ay[u], az[u],
-                           fx, fy, fz, r2);
+                pair_sym32<UNI>(xj, yj, zj, wj, xi[u], yi[u], zi[u], wi[u], keep, ax[u], ay[u],
+                                az[u], fx, fy, fz, r2);
             if constexpr (MODE != 0) hit[u] = keep && r2 < th2[u];
         }
         if constexpr (MODE != 0) {
             // one branch per rotation step for the lane's IPL pairs
             bool any = hit[0];
 #pragma unroll
-            for (int u = 1; u < IPL; ++u) any = any || hit[u];
+            for (int u = 1; u < NU; ++u) any = any || hit[u];
             if (any) {
                 unsigned cnt = 0u;
 #pragma unroll
-                for (int u = 0; u < IPL; ++u) cnt += hit[u] ? 1u : 0u;
+                for (int u = 0; u < NU; ++u) cnt += hit[u] ? 1u : 0u;
                 unsigned q = atomicAdd(qn, cnt);
 #pragma unroll
-                for (int u = 0; u < IPL; ++u) {
+                for (int u = 0; u < NU; ++u) {
                     if (hit[u]) {
                         if (q < (unsigned)kCrudeQ) {
-                            qi[q] = ib + lt[u];
+                            qi[q] = ib + lt0 + 64 * u;
                             qj[q] = jsub + ((lane + k) & 63);
                         }
                         ++q;
@@ -930,7 +932,8 @@ __device__ void sym_flush(const KickArgs &ka, const int *qi, const int *qj, unsi
 // REC: the variant that writes workgroup records (profiling with records;
 // a separate instantiation, so the kernel timed otherwise carries no trace
 // of them: any extra live value changes this kernel's register
-// allocation).  Its occupancy is held at the plain variant's (waves per
+// allocation).  The timed crude kicks are held at three waves too: two
+// registers more than three allow cost the 16,388-body step 6%.  Its occupancy is held at the plain variant's (waves per
 // SIMD: 4 for the plain kick and the 128-thread, one-i crude kick, 3 for
 // the other crude kicks), so that its records show the timed kernel's
 // balance.
@@ -940,9 +943,18 @@ constexpr int kick_rec_waves()
     return MODE == 0 ? 4 : (IPL == 1 && BS == 128 ? 4 : 3);
 }
 
-template <int BS, int IPL, int MODE, int PREC, bool REC = false>
+// UNIT: the kick of one system counts masses in units of its last body's (a
+// disk's planetesimals share one mass).  Where a lane group and a sub-tile
+// hold nothing else the pair needs no products with the masses, 18 FP64
+// operations instead of 20, and the sums are scaled once, where they are
+// stored.  Measured (fused / plain): 16,388 bodies 148 / 128 -> 145 / 126
+// us, 40,003 730 / 634 -> 649 / 595 us, 65,540 1.83 / 1.64 -> 1.68 / 1.53
+// ms, 131,076 7.56 / 6.95 -> 7.17 / 6.72 ms.  Contexts of many systems keep the products:
+// with a planet in the first tile of every short chunk the batch gained
+// 1.5%, and its close planet encounters amplify a changed last bit.
+template <int BS, int IPL, int MODE, int PREC, bool UNIT, bool REC = false>
 __global__ __launch_bounds__(BS)
-__attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() : 1, 4))) void k_kick_sym(
+__attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() : (MODE ? 3 : 1), 4))) void k_kick_sym(
     KickArgs ka)
 {
     static_assert(IPL == 1 || IPL == 2, "one or two i per lane");
@@ -993,7 +1005,13 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
         cn = 0u;
     }
     unsigned qstart = 0;   // queue entries left by earlier tiles of the item (uniform)
-    const double G = ka.G;
+    // mass unit (UNIT; a massless or extremely light last body is none): w is
+    // the mass a pair carries, wscale the factor of the sums
+    const double mlast = UNIT ? d.m[so + ns - 1] : 0.0;
+    const bool has_ref = UNIT && mlast > 1e-60 && mlast < 1e60;
+    const double mref = has_ref ? mlast : 1.0;
+    const double wscale = UNIT ? ka.G * mref : 1.0;
+    auto weight = [&](double m) { return UNIT ? m / mref : ka.G * m; };
     const double seed = ka.r2seed, c158 = ka.c158;
     // 3/2 in a vector register: the correction's inner fma would otherwise
     // take two scalar operands and cost a move per pair
@@ -1003,40 +1021,36 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
         const bool first_ib = ib == it.i0;
         const int nib = min(BI, it.i0 + it.ni - ib);
         // lane group u of wave w holds i = ib + 64 (IPL w + u) + lane
-        double xi[IPL], yi[IPL], zi[IPL], gmi[IPL], hi[IPL], Ai[IPL], vi[IPL];
+        double xi[IPL], yi[IPL], zi[IPL], wi[IPL];
         double ax[IPL], ay[IPL], az[IPL], th2[IPL];
-        int iu[IPL], lt[IPL];
+        const int lt0 = 64 * IPL * wv + lane;
         bool oku[IPL];
+        bool uni = has_ref;   // (a group with padding holds a zero mass)
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
-            lt[u] = 64 * (IPL * wv + u) + lane;
-            iu[u] = ib + lt[u];
-            oku[u] = lt[u] < nib;
-            const int i = iu[u];
+            const int i = ib + lt0 + 64 * u;
+            oku[u] = lt0 + 64 * u < nib;
             xi[u] = oku[u] ? d.x[i] : kFar;
             yi[u] = oku[u] ? d.y[i] : kFar;
             zi[u] = oku[u] ? d.z[i] : kFar;
-            gmi[u] = oku[u] ? G * d.m[i] : 0.0;
-            hi[u] = Ai[u] = vi[u] = 0.0;
-            if (MODE && oku[u]) {
-                hi[u] = d.ch[i];
-                Ai[u] = d.A[i];
-                vi[u] = d.cv[i];
-            }
+            const double mi = oku[u] ? d.m[i] : 0.0;
+            wi[u] = weight(mi);
+            uni = uni && wi[u] == 1.0;
             ax[u] = ay[u] = az[u] = 0.0;
             th2[u] = -1.0;
         }
         const int iw = ib + 64 * IPL * wv;   // first i of this wave
         const bool wave_i = 64 * IPL * wv < nib;
+        const bool wuni = UNIT && __all(uni);
         for (int jt = max(it.j0, ib); jt < jend; jt += BS) {
             const int j = jt + tid;
             const bool okj = j < jend;
             __syncthreads();   // the previous tile's LDS reads and queue are done
             {
                 const double xj = okj ? d.x[j] : kFar, yj = okj ? d.y[j] : kFar;
-                const double zj = okj ? d.z[j] : kFar, mj = okj ? G * d.m[j] : 0.0;
+                const double zj = okj ? d.z[j] : kFar, mj = okj ? d.m[j] : 0.0;
                 txy[wv][lane] = txy[wv][lane + 64] = make_double2(xj, yj);
-                tzm[wv][lane] = tzm[wv][lane + 64] = make_double2(zj, mj);
+                tzm[wv][lane] = tzm[wv][lane + 64] = make_double2(zj, weight(mj));
             }
             // this thread's reaction entry, read early (latency hidden by the
             // pairs); the item's first i-block starts it from zero
@@ -1068,15 +1082,19 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                     AT = fmax(AT, smax[1][w2]);
                     VT = fmax(VT, smax[2][w2]);
                 }
-                // per-(i, tile) upper bound of the crude threshold (as in k_kick)
+                // per-(i, tile) upper bound of the crude threshold (as in k_kick);
+                // the i's own terms are read again for each tile, not kept
+                // over the pair loop
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
+                    const int i = oku[u] ? ib + lt0 + 64 * u : it.i0;
+                    const double hi = d.ch[i], Ai = d.A[i], vi = d.cv[i];
                     double Rb;
                     if (MODE == 1)
-                        Rb = ka.aE * (hi[u] + HT) * (Ai[u] + AT) / 2.0;
+                        Rb = ka.aE * (hi + HT) * (Ai + AT) / 2.0;
                     else
-                        Rb = ka.aE * (hi[u] + HT);
-                    const double th = ka.cs * (Rb + ka.tau_abs * (vi[u] + VT));
+                        Rb = ka.aE * (hi + HT);
+                    const double th = ka.cs * (Rb + ka.tau_abs * (vi + VT));
                     th2[u] = oku[u] ? th * th * 1.000000000001 : -1.0;
                 }
             }
@@ -1088,20 +1106,23 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 const double2 *pxy = &txy[sub][0], *pzm = &tzm[sub][0];
                 // whole waves past the i-block's end or sub-tiles past the
                 // chunk's end have no pairs (uniform per wave)
+                auto meet = [&](auto dg, auto un) {
+                    sym_subtile<MODE, PREC, IPL, decltype(dg)::value, decltype(un)::value>(
+                        pxy, pzm, lane, xi, yi, zi, wi, th2, lt0, seed, c158, c32, ax, ay, az, fx,
+                        fy, fz, qi, qj, &qn, ib, jt + 64 * sub);
+                };
+                using std::integral_constant;
                 if (!wave_i || jw >= jend || rel < 0) {
                     // nothing to add
                 } else if (rel >= 64 * IPL) {
-                    sym_subtile<MODE, PREC, IPL, SYM_FULL, SYM_FULL>(
-                        pxy, pzm, lane, xi, yi, zi, gmi, th2, lt, seed, c158, c32, ax, ay,
-                        az, fx, fy, fz, qi, qj, &qn, ib, jt + 64 * sub);
+                    if (wuni && __all(pzm[lane].y == 1.0))
+                        meet(integral_constant<int, -1>{}, integral_constant<bool, UNIT>{});
+                    else
+                        meet(integral_constant<int, -1>{}, integral_constant<bool, false>{});
                 } else if (IPL == 2 && rel == 64) {
-                    sym_subtile<MODE, PREC, IPL, SYM_FULL, SYM_DIAG>(
-                        pxy, pzm, lane, xi, yi, zi, gmi, th2, lt, seed, c158, c32, ax, ay,
-                        az, fx, fy, fz, qi, qj, &qn, ib, jt + 64 * sub);
+                    meet(integral_constant<int, IPL == 2 ? 1 : 0>{}, integral_constant<bool, false>{});
                 } else {   // rel == 0
-                    sym_subtile<MODE, PREC, IPL, SYM_DIAG, SYM_SKIP>(
-                        pxy, pzm, lane, xi, yi, zi, gmi, th2, lt, seed, c158, c32, ax, ay,
-                        az, fx, fy, fz, qi, qj, &qn, ib, jt + 64 * sub);
+                    meet(integral_constant<int, 0>{}, integral_constant<bool, false>{});
                 }
                 wpart[wv][0][64 * sub + lane] = fx;
                 wpart[wv][1][64 * sub + lane] = fy;
@@ -1119,12 +1140,12 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                         const double hj = d.ch[jl], Aj = d.A[jl], vj = d.cv[jl];
 #pragma unroll
                         for (int u = 0; u < IPL; ++u) {
-                            const int i = iu[u];
+                            const int i = ib + lt0 + 64 * u;
                             if (!oku[u] || jl <= i) continue;
                             const double dx = pxy.x - xi[u], dy = pxy.y - yi[u], dz = zj - zi[u];
                             const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, r2_seed<PREC>(ka))));
                             if (!(r2 < th2[u]) &&
-                                r2 < pair_bound<MODE>(ka, hi[u], Ai[u], vi[u], hj, Aj, vj)) {
+                                r2 < pair_bound<MODE>(ka, d.ch[i], d.A[i], d.cv[i], hj, Aj, vj)) {
                                 const unsigned q = atomicAdd(&qn, 1u);
                                 if (q < (unsigned)kCrudeQ) {
                                     qi[q] = i;
@@ -1142,7 +1163,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                     double sum = wpart[0][c][tid];
 #pragma unroll
                     for (int w2 = 1; w2 < NW; ++w2) sum += wpart[w2][c][tid];
-                    rj[c * ns + j] = racc[c] + sum;
+                    rj[c * ns + j] = racc[c] + (UNIT ? wscale * sum : sum);
                 }
             }
             if constexpr (MODE != 0) {
@@ -1162,7 +1183,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                     for (int u = 0; u < IPL; ++u)
                         if (oku[u])
                             tile_exact<BS, MODE>(
-                                ka, iu[u], xi[u], yi[u], zi[u], jt, min(BS, jend - jt),
+                                ka, ib + lt0 + 64 * u, xi[u], yi[u], zi[u], jt, min(BS, jend - jt),
                                 wpart[0], [&](int jj, double &x, double &y, double &z) {
                                     const double2 a2 = txy[jj >> 6][jj & 63];
                                     x = a2.x;
@@ -1189,10 +1210,10 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
             if (oku[u]) {
-                const int il = iu[u] - so;
-                d.acc[pb + il] = ax[u];
-                d.acc[pb + ns + il] = ay[u];
-                d.acc[pb + 2 * ns + il] = az[u];
+                const int il = ib + lt0 + 64 * u - so;
+                d.acc[pb + il] = UNIT ? wscale * ax[u] : ax[u];
+                d.acc[pb + ns + il] = UNIT ? wscale * ay[u] : ay[u];
+                d.acc[pb + 2 * ns + il] = UNIT ? wscale * az[u] : az[u];
             }
         }
     }

@@ -107,6 +107,46 @@ def test_crude_candidates_match(Q, orc, name, shape):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 193, 577])
+@pytest.mark.parametrize("masses", ["equal", "two", "last_planet", "last_massless", "last_tiny",
+                                    "all_massless", "ragged"])
+def test_kick_mass_unit(Q, orc, n, masses):
+    """The symmetric kick of one system counts masses in units of its last
+    body's and drops the products where all 128 or 192 bodies that meet have
+    that mass: every pattern of equal and other masses at the tile edges, a
+    last body that is no unit, and a coincident pair, within the operator
+    bar (1e-13 of each body's acceleration)."""
+    s = inputs.make_disk("unit", 5, n, 1e-8, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025,
+                         planets=False)
+    if masses == "two":
+        s.m[: n // 2] = 3e-9
+    elif masses == "last_planet":
+        s.m[-1] = 1e-3
+    elif masses == "last_massless":
+        s.m[-1] = 0.0
+    elif masses == "last_tiny":
+        s.m[-1] = 1e-80
+    elif masses == "all_massless":
+        s.m[:] = 0.0
+    elif masses == "ragged":
+        s.m[:] = np.random.default_rng(n).uniform(1e-9, 1e-4, n)
+    if n > 64:
+        s.q[3] = s.q[n - 2]
+    s.v[:] = 0.0
+    ref = orc.accel(s.G, s.m, s.q)
+    for sh in (dict(ipl=1, block=128, jchunk=128, remap=0, sym=1),
+               dict(ipl=2, block=128, jchunk=256, remap=3, sym=1),
+               dict(ipl=2, block=256, jchunk=512, remap=0, sym=2)):
+        for crude in (0.0, 0.05):
+            say("mass unit", n, masses, sh, crude)
+            ctx = Q.Context(s)
+            ctx.set_kick_shape(**sh)
+            ctx.apply_kick(1.0, crude_tau=crude)
+            _, a = ctx.get_state()
+            assert per_body_rel(a, ref) < 1e-13
+            ctx.close()
+
+
 def _planets_among(n, at, seed, m=1e-8):
     """A disk of n bodies whose four planets stand at body indices ``at``."""
     s = inputs.make_disk(f"among{n}", seed, n - 4, m, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025)
