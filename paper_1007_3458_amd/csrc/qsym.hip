@@ -1143,6 +1143,59 @@ hipError_t enqueue_step_last(qsym_ctx *c, double tau, hipStream_t st)
     return enqueue_last_drift(c, tau, st);
 }
 
+// Kick shape of both kicks until the autotuner or a tuned table replaces it.
+//
+// One system of 5000 bodies or more: the symmetric kick.  Its items should
+// number some 1500 (about six a compute unit), so they grow with the system:
+// 128, 256, then 512 i against enough j for that, up to 1536 j (longer items
+// leave a ragged last round), largest first and XCD-aware; and i-ranges of
+// as many blocks as the partial slots need.  Measured against
+// the full-matrix shape, fused / plain kick in us: 4100 bodies 28.8 / 24.3
+// against 29.5 / 23.7 (so the line is at 5000), 8200 53 / 47 against 76 / 64,
+// 12,000 94 / 81 against 135 / 114, 25,000 281 / 252 against 528 / 458, 40,003
+// 649 / 595 against 1293 / 1091, 90,000 3353 / 3014 against 6186 / 5502.
+//
+// Otherwise the full matrix, one i per lane, with j-chunks that give the
+// grid 4096 workgroups where the size allows: small kicks are bound by the
+// length of one workgroup's chain, which is shorter without the reactions,
+// and the sums of a context of many systems keep their order.
+Shape default_shape(qsym_ctx *c)
+{
+    Shape sh;
+    const long long jmin = c->L.jchunk_min;
+    const long long n = c->ntot;
+    if (c->nsys == 1 && n >= 5000) {
+        sh.block = n < 10000 ? 128 : (n < 14000 ? 256 : (n < 20000 ? 128 : 256));
+        sh.ipl = n < 14000 ? 1 : 2;
+        sh.remap = 3;
+        const long long BI = (long long)sh.block * sh.ipl;
+        const long long want = std::min<long long>(n * n / (3000 * BI), 1536);
+        const long long jc = std::max((want + BI / 2) / BI * BI, (jmin + BI - 1) / BI * BI);
+        sh.jchunk = std::max(jc, BI);
+        const long long slots = partial_slots(n, jmin) - (n + sh.jchunk - 1) / sh.jchunk;
+        sh.sym = 1;
+        while (sh.sym < 8 && (n + BI * sh.sym - 1) / (BI * sh.sym) > slots) sh.sym *= 2;
+        if ((n + BI * sh.sym - 1) / (BI * sh.sym) <= slots) return sh;
+    }
+    sh.block = 128;
+    sh.ipl = 1;
+    sh.remap = 0;
+    sh.sym = 0;
+    long long jc = 8192;
+    while (jc > jmin) {
+        long long items = 0;
+        for (int s = 0; s < c->nsys; ++s) {
+            const long long ns = nsys_bodies(c->off, s);
+            items += ((ns + 127) / 128) * ((ns + jc - 1) / jc);
+        }
+        if (items >= 4096) break;
+        jc /= 2;
+    }
+    sh.jchunk = std::max<long long>(jc, jmin);
+    sh.jchunk = (sh.jchunk + 127) / 128 * 128;
+    return sh;
+}
+
 void enter(qsym_ctx *c)
 {
     (void)hipEventRecord(c->ev_in, c->ustream);
@@ -1391,27 +1444,7 @@ int qsym_create(const qsym_params *p, int32_t nsys, const int64_t *offsets, cons
                          hipMemcpyHostToDevice, st) == hipSuccess;
     ok &= hipStreamSynchronize(st) == hipSuccess;
     if (!ok) return bail(QSYM_EHIP, "table upload");
-    // default kick shapes (the autotuner or a tuned table replaces them):
-    // block 128, one i per lane, j-split so that the grid has >= 4096
-    // workgroups where the size allows
-    for (int w = 0; w < 2; ++w) {
-        Shape &sh = c->shape[w];
-        sh.block = 128;
-        sh.ipl = 1;
-        sh.remap = 0;
-        long long jc = 8192;
-        while (jc > c->L.jchunk_min) {
-            long long items = 0;
-            for (int s = 0; s < nsys; ++s) {
-                const long long n = nsys_bodies(c->off, s);
-                items += ((n + 127) / 128) * ((n + jc - 1) / jc);
-            }
-            if (items >= 4096) break;
-            jc /= 2;
-        }
-        sh.jchunk = std::max<long long>(jc, c->L.jchunk_min);
-        sh.jchunk = (sh.jchunk + 127) / 128 * 128;
-    }
+    c->shape[0] = c->shape[1] = default_shape(c);
     if (upload_shape(c, 0) != QSYM_OK || upload_shape(c, 1) != QSYM_OK) {
         g_noctx_err = c->err;
         return bail(QSYM_EINVAL, "kick shape upload");

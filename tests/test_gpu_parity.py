@@ -147,6 +147,29 @@ def test_kick_mass_unit(Q, orc, n, masses):
             ctx.close()
 
 
+@pytest.mark.parametrize("n", [4999, 5000, 9999, 10000, 13999, 14000, 19999, 20000, 60001])
+def test_default_kick_shapes(Q, orc, n):
+    """The default shapes on both sides of every line of the rule: forces of
+    sampled bodies (1e-13) and a hybrid step that reports no error."""
+    s = inputs.scaled_disk(n - 4, 6)
+    rows = np.unique(np.concatenate([np.arange(0, n, n // 60), [n - 1]]))
+    ref = orc.accel_rows(s.G, s.m, s.q, rows)
+    v = s.v.copy()
+    s.v[:] = 0.0
+    ctx = Q.Context(s, shapes=None)
+    say("default shapes", n, ctx.kick_shape(0), ctx.kick_shape(1))
+    assert (ctx.kick_shape(0)["sym"] > 0) == (n >= 5000)
+    for crude in (0.0, 0.05):
+        ctx.set_state(s.m, s.h, s.q, s.v)
+        ctx.apply_kick(1.0, crude_tau=crude)
+        assert per_body_rel(ctx.get_state()[1][rows], ref) < 1e-13
+    ctx.set_state(s.m, s.h, s.q, v)
+    ctx.step(0.05, 1)
+    ctx.sync()
+    assert np.all(np.isfinite(ctx.get_state()[0]))
+    ctx.close()
+
+
 def _planets_among(n, at, seed, m=1e-8):
     """A disk of n bodies whose four planets stand at body indices ``at``."""
     s = inputs.make_disk(f"among{n}", seed, n - 4, m, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025)
