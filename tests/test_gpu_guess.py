@@ -290,3 +290,27 @@ def test_packaged_weights_gain(Q):
     a, b = it1.cpu().numpy(), it2.cpu().numpy()
     say(f"packaged weights: mean {a.mean():.3f} -> {b.mean():.3f}")
     assert np.all(b > 0) and b.mean() < 0.9 * a.mean()
+
+
+@pytest.mark.parametrize("z", [2.0 ** -30, 2.0 ** -10, 2.0 ** -3, 1.0])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_stumpff_series_lengths(Q, orc, z, mixed, mode):
+    """Roots on both sides of the values of alpha x^2 where the Stumpff series
+    changes its length (2^-10, 2^-3, 1), whole waves at one value and waves
+    that mix it with large ones: the oracle's, which sums every term, to 4
+    ulp."""
+    n = 200
+    a = np.full(n, 7.0)
+    e = np.linspace(0.0, 0.3, n)
+    ang = np.random.default_rng(3).uniform(0.0, 2.0 * np.pi, (3, n))
+    q, v = inputs.elements_to_cartesian(1.0, a, e, 0.1 * e, ang[0], ang[1], ang[2])
+    # x = sqrt(a) dE, alpha x^2 = dE^2, dE ~ n dt
+    zz = z * (1.0 + np.linspace(-1e-3, 1e-3, n))
+    if mixed:
+        zz[::7] = 2.0
+    dt = np.sqrt(zz) * a ** 1.5
+    x, it = Q.kepler_solve(1.0, Q.state_tensor(q, v), dt, mode)
+    xo, _, fails = orc.kepler_roots(1.0, q, v, dt, mode)
+    assert fails == 0 and bool((it > 0).all())
+    assert np.max(np.abs(x.cpu().numpy() / xo - 1.0)) < 4 * 2.3e-16
