@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "qsym_kernels.hpp"
+#include "qsym_small.hpp"
 #include "qsym_sweep.hpp"
 
 using namespace qsym;
@@ -54,6 +55,8 @@ struct Layout {
            off_swpart = 0;
     long long sw_nb = 1;       // grid-sweep buckets
     size_t off_hw = 0, off_ctr = 0, off_kstat = 0, off_E = 0, off_guess = 0;
+    size_t off_small = 0;      // counters and figures of k_small_steps
+    bool small = false;        // every system has at most kSmallMax bodies
     size_t off_erec = 0, off_ewcol = 0, off_ewrec = 0, off_sysu0 = 0, off_sysr0 = 0;
     int e_waves = 4;           // waves of k_energy_pairs (a multiple of 4)
     size_t total = 0;
@@ -227,6 +230,9 @@ Layout make_layout(const qsym_params &p, const std::vector<long long> &off)
     take(L.off_swpart, 3 * (size_t)L.nchunks * D);
     take(L.off_ctr, (size_t)C_COUNT * sizeof(unsigned long long));
     take(L.off_kstat, (size_t)kStatStripes * kStatStride * sizeof(unsigned long long));
+    L.small = nsys > 0;
+    for (int s = 0; s < nsys; ++s) L.small = L.small && off[s + 1] - off[s] <= kSmallMax;
+    take(L.off_small, L.small ? (SW_COUNT + (size_t)nsys * SS_COUNT) * sizeof(unsigned long long) : 8);
     L.e_waves = energy_waves(off);
     take(L.off_erec, (size_t)kERec * (L.e_waves + nsys) * D);
     take(L.off_ewcol, (size_t)(L.e_waves + 1) * sizeof(long long));
@@ -1274,6 +1280,60 @@ hipError_t enqueue_swapped_last(qsym_ctx *c, double tau, hipStream_t st)
     return run_drift(c, tau / 2.0, 0, 0.0, 0, st, P_DRIFT2, 1);
 }
 
+// Whether the steps run in k_small_steps: systems of at most kSmallMax bodies
+// and full-matrix kicks (whose partial sums it reproduces), the crude sweep
+// fused, no per-kernel timings asked for.  A few systems of more than 192
+// bodies are left to the step's kernels, which spread a kick over several
+// compute units: one system of 200 / 256 bodies took 60 / 78 us a step in one
+// workgroup against 70 / 72, 64 of 250 bodies 103 against 148.
+bool small_steps(const qsym_ctx *c)
+{
+    if (!c->L.small || c->p.sweep || c->profile || c->shape[0].sym || c->shape[1].sym) return false;
+    int nmax = 0;
+    for (int s = 0; s < c->nsys; ++s) nmax = std::max(nmax, nsys_bodies(c->off, s));
+    return nmax <= 192 || c->nsys >= 16;
+}
+
+hipError_t run_small(qsym_ctx *c, double tau, int64_t nsteps, int kind)
+{
+    SmallArgs a{};
+    a.d = c->d;
+    a.w = (unsigned long long *)(c->base + c->L.off_small);
+    a.st = a.w + SW_COUNT;
+    a.h = HermArgs{c->d, tau, c->p.G, c->p.epsH, c->p.eta, c->p.eta_s, c->p.max_substeps};
+    a.aE = c->p.aE;
+    a.aH = c->p.aH;
+    a.cs = c->p.crude_safety;
+    a.planet_mass = c->p.planet_mass;
+    a.r2seed = 1e-200;
+    a.c158 = 1.875;
+    a.c32 = 1.5;
+    a.cap = c->L.cap;
+    for (int w = 0; w < 2; ++w) a.jc[w] = (int)std::min<long long>(c->shape[w].jchunk, kSmallMax);
+    a.hill_mode = c->p.hill_mode;
+    a.kepler_mode = c->p.kepler_mode;
+    a.nsys = c->nsys;
+    for (int64_t k = 0; k < nsteps; k += kSmallSteps) {
+        a.nsteps = (int)std::min<int64_t>(nsteps - k, kSmallSteps);
+        a.first = k == 0;
+        // with several systems: the second launch takes the steps again when
+        // one of them overflowed its encounter segment, else it does nothing
+        for (a.redo = 0; a.redo <= (c->nsys > 1 && kind == 0 ? 1 : 0); ++a.redo) {
+            const dim3 g(c->nsys), b(kSmallThreads);
+            if (kind == 0) {
+                if (c->p.precision == 0) hipLaunchKernelGGL((k_small_steps<0, false>), g, b, 0, c->stream, a);
+                else hipLaunchKernelGGL((k_small_steps<1, false>), g, b, 0, c->stream, a);
+            } else {
+                if (c->p.precision == 0) hipLaunchKernelGGL((k_small_steps<0, true>), g, b, 0, c->stream, a);
+                else hipLaunchKernelGGL((k_small_steps<1, true>), g, b, 0, c->stream, a);
+            }
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
+}
+
 // nsteps steps of one kind (0 hybrid, 1 swapped): eager launches in
 // profiling mode, else one captured step replayed
 int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
@@ -1283,6 +1343,11 @@ int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
         return fail(c, QSYM_EINVAL, "kepler_mode 2 needs weights (qsym_set_guess)");
     if (nsteps == 0 || c->ntot == 0) return QSYM_OK;
     enter(c);
+    if (small_steps(c)) {
+        HIPCHK(c, run_small(c, tau, nsteps, kind));
+        leave(c);
+        return QSYM_OK;
+    }
     // a call of n steps: the first drift, then n - 1 times the step body
     // with the fused drift between steps, then the last body and drift
     using Enq = hipError_t (*)(qsym_ctx *, double, hipStream_t);

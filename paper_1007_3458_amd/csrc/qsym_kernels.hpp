@@ -373,22 +373,34 @@ __device__ __forceinline__ double wave_max(double v)
 // Crude sweep, exact form (Sec. 2.4 reading): evaluated only for the pairs
 // that passed the per-tile bound; same operands and operation order as the
 // definition:  |Q_j-Q_i|^2 < (c_s (R_up + |tau| (ve_i + ve_j)))^2.
-// X, Y, Z: the positions the sweep runs at (the kick's, or their snapshot).
+struct CrudeBody {
+    double x, y, z, h, A, cv;
+};
+
+__device__ __forceinline__ bool crude_test(int hill_mode, double aE, double cs, double tau_abs,
+                                           const CrudeBody &bi, const CrudeBody &bj)
+{
+    const double dx = bj.x - bi.x;
+    const double dy = bj.y - bi.y;
+    const double dz = bj.z - bi.z;
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    double Rup;
+    if (hill_mode == 0)
+        Rup = aE * (bi.h + bj.h) * (bi.A + bj.A) / 2.0;
+    else
+        Rup = aE * (bi.h * bi.A + bj.h * bj.A);
+    const double lim = cs * (Rup + tau_abs * (bi.cv + bj.cv));
+    return r2 < lim * lim;
+}
+
+// X, Y, Z: the positions the sweep runs at (the kick's, or their snapshot)
 __device__ __forceinline__ bool crude_pass(const Dev &d, const double *X, const double *Y,
                                            const double *Z, int hill_mode, double aE, double cs,
                                            double tau_abs, int i, int j)
 {
-    const double dx = X[j] - X[i];
-    const double dy = Y[j] - Y[i];
-    const double dz = Z[j] - Z[i];
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    double Rup;
-    if (hill_mode == 0)
-        Rup = aE * (d.h[i] + d.h[j]) * (d.A[i] + d.A[j]) / 2.0;
-    else
-        Rup = aE * (d.h[i] * d.A[i] + d.h[j] * d.A[j]);
-    const double lim = cs * (Rup + tau_abs * (d.cv[i] + d.cv[j]));
-    return r2 < lim * lim;
+    return crude_test(hill_mode, aE, cs, tau_abs,
+                      CrudeBody{X[i], Y[i], Z[i], d.h[i], d.A[i], d.cv[i]},
+                      CrudeBody{X[j], Y[j], Z[j], d.h[j], d.A[j], d.cv[j]});
 }
 
 __device__ __forceinline__ void crude_exact(const KickArgs &ka, int i, int j)
@@ -405,18 +417,24 @@ __device__ __forceinline__ void crude_exact(const KickArgs &ka, int i, int j)
 // 1e-200 seed (so the own pair gives 0 * finite = 0 and r^2 >= 1e-184 is
 // unchanged); the correction is the factor w = 1 + e (3/2 + 15/8 e), so the
 // term costs 17 VALU instructions: 3 add, 9 fma, 4 mul, 1 rsq.
-__device__ __forceinline__ void pair64(const double4 &pj, double xi, double yi, double zi,
-                                       double seed, double c158, double c32, double &ax,
-                                       double &ay, double &az, double &r2)
+__device__ __forceinline__ double pair_factor64(double gm, double dx, double dy, double dz,
+                                                double seed, double c158, double c32, double &r2)
 {
-    const double dx = pj.x - xi, dy = pj.y - yi, dz = pj.z - zi;
     r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, seed)));
     const double y0 = __builtin_amdgcn_rsq(r2);
     const double y2 = y0 * y0;
     const double e = fma(-r2, y2, 1.0);
     // r^-3 = y0^3 (1 - e)^(-3/2) = y0^3 (1 + 3/2 e + 15/8 e^2 + O(e^3)), |e| ~ 1e-7
     const double w = fma(e, fma(e, c158, c32), 1.0);
-    const double ms = (y2 * y0) * (pj.w * w);
+    return (y2 * y0) * (gm * w);
+}
+
+__device__ __forceinline__ void pair64(const double4 &pj, double xi, double yi, double zi,
+                                       double seed, double c158, double c32, double &ax,
+                                       double &ay, double &az, double &r2)
+{
+    const double dx = pj.x - xi, dy = pj.y - yi, dz = pj.z - zi;
+    const double ms = pair_factor64(pj.w, dx, dy, dz, seed, c158, c32, r2);
     ax = fma(ms, dx, ax);
     ay = fma(ms, dy, ay);
     az = fma(ms, dz, az);
@@ -430,16 +448,61 @@ __device__ __forceinline__ void pair64(const double4 &pj, double xi, double yi, 
 // double loses nothing a float product would keep, and saves the mass's
 // narrowing), and the sum is accumulated in FP64.  The 1e-24 seed keeps
 // the own pair finite (r^-3 = 1e36 < FLT_MAX) and changes no physical pair.
+__device__ __forceinline__ double pair_factor32(double gm, double dx, double dy, double dz,
+                                                double &r2)
+{
+    r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, 1e-24)));
+    const float y = __builtin_amdgcn_rsqf((float)r2);
+    return gm * (double)(y * y * y);
+}
+
 __device__ __forceinline__ void pair32(const double4 &pj, double xi, double yi, double zi,
                                        double &ax, double &ay, double &az, double &r2)
 {
     const double dx = pj.x - xi, dy = pj.y - yi, dz = pj.z - zi;
-    r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, 1e-24)));
-    const float y = __builtin_amdgcn_rsqf((float)r2);
-    const double ms = pj.w * (double)(y * y * y);
+    const double ms = pair_factor32(pj.w, dx, dy, dz, r2);
     ax = fma(ms, dx, ax);
     ay = fma(ms, dy, ay);
     az = fma(ms, dz, az);
+}
+
+// the factors G m r^-3 of Q pairs side by side, operation by operation (the
+// compiler keeps the order of the source, and pair after pair would be Q
+// chains in a row): each the bits of pair_factor64 / pair_factor32
+template <int Q, int PREC>
+__device__ __forceinline__ void pair_factors(const double (&gm)[Q], const double (&dx)[Q],
+                                             const double (&dy)[Q], const double (&dz)[Q],
+                                             double seed, double c158, double c32, double (&r2)[Q],
+                                             double (&ms)[Q])
+{
+    const double s0 = PREC == 0 ? seed : 1e-24;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r2[q] = fma(dx[q], dx[q], s0);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r2[q] = fma(dy[q], dy[q], r2[q]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r2[q] = fma(dz[q], dz[q], r2[q]);
+    if constexpr (PREC == 0) {
+        double y0[Q], y2[Q], e[Q], w[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) y0[q] = __builtin_amdgcn_rsq(r2[q]);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) y2[q] = y0[q] * y0[q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) e[q] = fma(-r2[q], y2[q], 1.0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) w[q] = fma(e[q], c158, c32);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) w[q] = fma(e[q], w[q], 1.0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ms[q] = (y2[q] * y0[q]) * (gm[q] * w[q]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const float y = __builtin_amdgcn_rsqf((float)r2[q]);
+            ms[q] = gm[q] * (double)(y * y * y);
+        }
+    }
 }
 
 // the seed of r^2 in the pair terms (the test of split_large's bodies takes
@@ -2321,6 +2384,32 @@ struct SetLds {
     double *x, *y, *z, *u, *v, *w, *m;
 };
 
+// the state a set is integrated in: the snapshot (q0, v0) it starts from and
+// the arrays its end state goes to (global memory, or a workgroup's LDS)
+struct HermState {
+    const double *x0, *y0, *z0, *vx0, *vy0, *vz0, *m;
+    double *x, *y, *z, *vx, *vy, *vz;
+};
+
+// one set: its n members (indices into the state's arrays), r_crit and G m0
+struct HermSet {
+    const int *mem;
+    int n;
+    double rc, mu;
+};
+
+__device__ __forceinline__ HermState herm_state(const Dev &d)
+{
+    return HermState{d.x0, d.y0, d.z0, d.vx0, d.vy0, d.vz0, d.m, d.x, d.y, d.z, d.vx, d.vy, d.vz};
+}
+
+__device__ __forceinline__ HermSet herm_set(const Dev &d, double G, int sidx)
+{
+    const int *mem = d.set_mem + __builtin_amdgcn_readfirstlane(d.set_start[sidx]);
+    return HermSet{mem, __builtin_amdgcn_readfirstlane(d.set_count[sidx]), d.set_rc[sidx],
+                   G * d.sys_m0[d.body_sys[mem[0]]]};
+}
+
 // One level of the sums over aligned lane groups: every lane adds the value
 // of its partner in the next larger group.  Within a row of 16 the
 // partners come through DPP (quad_perm [1,0,3,2] and [2,3,0,1]: the other
@@ -2571,13 +2660,11 @@ __device__ __forceinline__ double wave_uniform(double v)
 // slice.  Same steps as the workgroup version below (corrections at q0
 // and q1, PEC Hermite with one shared step), with no global memory traffic
 // inside the substep loop.
-__device__ void hermite_set_wave(const HermArgs &a, int sidx, const SetLds &S, int lane,
-                                 int &nsub_out, int &fail_out)
+__device__ void hermite_set_wave(const HermArgs &a, const HermState &d, const HermSet &hs,
+                                 const SetLds &S, int lane, int &nsub_out, int &fail_out)
 {
-    const Dev &d = a.d;
-    const int b0 = __builtin_amdgcn_readfirstlane(d.set_start[sidx]);
-    const int n = __builtin_amdgcn_readfirstlane(d.set_count[sidx]);
-    const double rc = d.set_rc[sidx];
+    const int n = __builtin_amdgcn_readfirstlane(hs.n);
+    const double rc = hs.rc;
     nsub_out = 0;
     fail_out = 0;
     if (n < 1 || n > kWaveMax) return;   // the set kernel lists 1..kWaveMax members here
@@ -2586,8 +2673,8 @@ __device__ void hermite_set_wave(const HermArgs &a, int sidx, const SetLds &S, i
     const int k = lane / L, l = lane % L;
     const bool mine = k < n;
     const int kk = mine ? k : 0;   // idle lanes shadow member 0; their results are dropped
-    const int i = d.set_mem[b0 + kk];
-    const double mu = a.G * d.sys_m0[d.body_sys[i]];
+    const int i = hs.mem[kk];
+    const double mu = hs.mu;
     const double half = a.tau / 2.0;
     double X[3] = {d.x0[i], d.y0[i], d.z0[i]};
     if (mine && l == 0) {
@@ -2700,21 +2787,19 @@ __device__ __forceinline__ double block_min_waves(double v, double *red)
 // J) in registers of those lanes, the staged set in LDS.  Same steps and
 // arithmetic as hermite_set_wave; per substep three barriers: the staged
 // prediction written, read, and the step-size minimum.
-__device__ void hermite_set_block(const HermArgs &a, int sidx, const SetLds &S, double *red,
-                                  int &nsub_out, int &fail_out)
+__device__ void hermite_set_block(const HermArgs &a, const HermState &d, const HermSet &hs,
+                                  const SetLds &S, double *red, int &nsub_out, int &fail_out)
 {
-    const Dev &d = a.d;
     const int t = threadIdx.x;
-    const int b0 = __builtin_amdgcn_readfirstlane(d.set_start[sidx]);
-    const int n = __builtin_amdgcn_readfirstlane(d.set_count[sidx]);
-    const double rc = d.set_rc[sidx];
+    const int n = __builtin_amdgcn_readfirstlane(hs.n);
+    const double rc = hs.rc;
     int L = 1;
     while (L < 64 && 2 * L * n <= kHermThreads) L <<= 1;
     const int k = t / L, l = t % L;
     const bool mine = k < n;
     const int kk = mine ? k : 0;   // idle groups shadow member 0; their results are dropped
-    const int i = d.set_mem[b0 + kk];
-    const double mu = a.G * d.sys_m0[d.body_sys[i]];
+    const int i = hs.mem[kk];
+    const double mu = hs.mu;
     const double half = a.tau / 2.0;
     double X[3] = {d.x0[i], d.y0[i], d.z0[i]};
     if (mine && l == 0) {
@@ -2845,7 +2930,8 @@ __global__ __launch_bounds__(kHermThreads) void k_hermite(HermArgs a)
         const int sidx = d.set_list[d.setcap - 1 - q];
         if (d.set_count[sidx] > kCoopMin) continue;   // the grid phase takes it
         int nsub, fail;
-        hermite_set_block(a, sidx, SetLds{s_x, s_y, s_z, s_u, s_v, s_w, s_m}, lds, nsub, fail);
+        hermite_set_block(a, herm_state(d), herm_set(d, a.G, sidx),
+                          SetLds{s_x, s_y, s_z, s_u, s_v, s_w, s_m}, lds, nsub, fail);
         if (t == 0) {
             nsub_b += nsub;
             fail_b |= fail;
@@ -2872,7 +2958,7 @@ __global__ __launch_bounds__(kHermThreads) void k_hermite(HermArgs a)
     int nsub_w = 0, fail_w = 0;
     for (int q = rank * wpb + w; q < nsmall; q += nwg * wpb) {
         int nsub, fail;
-        hermite_set_wave(a, d.set_list[q], S, lane, nsub, fail);
+        hermite_set_wave(a, herm_state(d), herm_set(d, a.G, d.set_list[q]), S, lane, nsub, fail);
         nsub_w += nsub;
         fail_w |= fail;
     }
