@@ -340,7 +340,7 @@ int qsym_guess_grad(qsym_guess_trainer *tr, const float *weights, const float *f
 /* qsym_guess_grad without allocation, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving or training
  * loops, harnesses that forbid it): no trainer; the partial sums of its
- * waves and the loss accumulator live in a static device array of
+ * workgroups and the loss accumulator live in a static device array of
  * 1.28 MB that each GPU holds from the first call on it until the process
  * ends.  weights (device, QSYM_GUESS_WEIGHTS floats), feat (device, rows of
  * ld floats as for qsym_guess_grad) and grad (device [1249], output) belong

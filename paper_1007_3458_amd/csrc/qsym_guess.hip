@@ -19,9 +19,8 @@ using namespace qsym;
 
 namespace {
 
-constexpr int kGRow = 140;                  // floats per sample row in LDS (12 banks mod 32)
-constexpr int kGPart = kGuessParams + 1;    // gradient sums + loss sum of one wave
-constexpr int kGMaxParts = 4096;            // waves of one gradient launch
+constexpr int kGPart = kGuessParams + 1;    // gradient sums + loss sum of one workgroup
+constexpr int kGMaxParts = 4096;            // workgroups of one gradient launch
 constexpr int kGMomBlocks = 1024;           // blocks of the moments reduction
 constexpr int kGMaxEpochs = 4096;
 
@@ -162,125 +161,190 @@ __global__ void k_guess_scalers(const double *__restrict__ part, int nb, long lo
     }
 }
 
-// Loss gradient sums over n samples, one wave per 64-sample tile (tiles
-// strided over the grid).  Each lane runs one sample forward and back; the
-// per-sample factors go to LDS and the wave then forms the sums over its
-// tile: the 32 x 32 second-layer block as a 4 x 4 register tile per lane,
-// the first layer, biases and output weights per first-layer/second-layer
-// unit.  part[wave] receives sum e dO/dw (e = o - target; the factor 2/n is
-// applied by the update) and sum e^2.
-__global__ __launch_bounds__(64) void k_guess_grad(const float *__restrict__ w,
-                                                   const float *__restrict__ feat, long long ld,
-                                                   long long n, float *__restrict__ part)
+// Loss gradient sums over n samples on the matrix cores: a workgroup of four
+// waves takes tiles of 64 samples (strided over the grid), a wave 16 of them.
+// All products are FP32 16x16x4 MFMA steps (A: row l % 16, k = l / 16 of lane
+// l; B: column l % 16, k = l / 16; C: rows 4 (l / 16) + 0..3, column l % 16).
+//
+// Forward and back, a column is a sample and a row a unit: the four rows a
+// lane holds of one result are the k = l / 16 terms of four steps of the next
+// product, once the columns of its weights are taken in that order (k of
+// step r: 4 (l / 16) + r), so layer follows layer without a move.  The
+// gradient sums run over samples; for them the unit rows go through LDS once,
+// transposed.  b1, b2, w3 and w1 take a product each whose B holds a column of
+// ones, the errors or the inputs.
+//
+// A lane per sample, 1024 fma in a row per layer on 128 waves, was bound by
+// that chain: 65 us at 8192 samples (of which the products need 0.7 us at the
+// card's FP32 rate), this 8.0 us.  part[workgroup] receives sum e dO/dw (e
+// = o - target; the factor 2/n is applied by the update) and sum e^2.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kGWaves = 4;
+constexpr int kGStride = 36;   // floats per sample row of the transposed units (16-byte rows)
+
+struct GradWave {
+    float h1[16][kGStride], h2[16][kGStride], d1[16][kGStride], d2[16][kGStride];
+    float in[16][8];   // standardised inputs, 1, e, 0, 0
+};
+
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c)
 {
-    __shared__ __align__(16) float rows[64 * kGRow];
-    const int l = threadIdx.x;
-    const int k0 = 4 * (l >> 3), c0 = 4 * (l & 7), u = l & 31;
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__global__ __launch_bounds__(64 * kGWaves) void k_guess_grad(const float *__restrict__ w,
+                                                             const float *__restrict__ feat,
+                                                             long long ld, long long n,
+                                                             float *__restrict__ part)
+{
+    __shared__ __align__(16) union {
+        GradWave wave[kGWaves];
+        float sum[kGWaves][kGPart];
+    } L;
+    const int t = threadIdx.x, l = t & 63, wv = t >> 6;
+    const int u = l & 15, g = l >> 4;
+    GradWave &S = L.wave[wv];
     const float *sc = w + kGuessParams;
-    float acc[4][4] = {};
-    float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, lsum = 0.f;
-    float gw1[4] = {0.f, 0.f, 0.f, 0.f};
-    for (long long tile = blockIdx.x; tile * 64 < n; tile += gridDim.x) {
-        const long long s = tile * 64 + l;
-        const bool valid = s < n;
-        float in[4], yt = 0.f;
+    // weights in operand order: w1 rows, w2 rows and columns, biases and w3 in
+    // the rows a lane holds
+    float a1[2], a2[2][2][4], at[2][2][4];
+    f32x4 b1[2], b2[2], w3[2];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) in[c] = valid ? (feat[c * ld + s] - sc[c]) / sc[4 + c] : 0.f;
-        if (valid) yt = (feat[4 * ld + s] - sc[8]) / sc[9];
-        float h1[32], h2[32];
+    for (int m = 0; m < 2; ++m) {
+        a1[m] = w[kGW1 + 4 * (16 * m + u) + g];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            float a = w[kGB1 + k];
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) a = fmaf(w[kGW1 + 4 * k + c], in[c], a);
-            h1[k] = tanh_fast(a);
-        }
-        float o = w[kGB3];
-#pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            float a = w[kGB2 + k];
-#pragma unroll
-            for (int c = 0; c < 32; ++c) a = fmaf(w[kGW2 + 32 * k + c], h1[c], a);
-            h2[k] = tanh_fast(a);
-            o = fmaf(w[kGW3 + k], h2[k], o);
-        }
-        const float e = valid ? o - yt : 0.f;
-        float *row = rows + l * kGRow;
-        float d2[32];
-#pragma unroll
-        for (int k = 0; k < 32; ++k) d2[k] = e * w[kGW3 + k] * (1.f - h2[k] * h2[k]);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            *(float4 *)(row + 4 * q) = make_float4(h1[4 * q], h1[4 * q + 1], h1[4 * q + 2], h1[4 * q + 3]);
-            *(float4 *)(row + 32 + 4 * q) =
-                make_float4(d2[4 * q], d2[4 * q + 1], d2[4 * q + 2], d2[4 * q + 3]);
-            *(float4 *)(row + 96 + 4 * q) =
-                make_float4(h2[4 * q], h2[4 * q + 1], h2[4 * q + 2], h2[4 * q + 3]);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            float d1[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 4 * q + j;
-                float b = 0.f;
-#pragma unroll
-                for (int k = 0; k < 32; ++k) b = fmaf(w[kGW2 + 32 * k + c], d2[k], b);
-                d1[j] = b * (1.f - h1[c] * h1[c]);
+            for (int r = 0; r < 4; ++r) {
+                a2[m][k][r] = w[kGW2 + 32 * (16 * m + u) + 16 * k + 4 * g + r];
+                at[m][k][r] = w[kGW2 + 32 * (16 * k + 4 * g + r) + 16 * m + u];
             }
-            *(float4 *)(row + 64 + 4 * q) = make_float4(d1[0], d1[1], d1[2], d1[3]);
-        }
-        *(float4 *)(row + 128) = make_float4(in[0], in[1], in[2], in[3]);
-        row[132] = e;
-        row[133] = e * e;
-        __syncthreads();
-#pragma unroll 4
-        for (int t = 0; t < 64; ++t) {
-            const float *rt = rows + t * kGRow;
-            const float4 dv = *(const float4 *)(rt + 32 + k0);
-            const float4 hv = *(const float4 *)(rt + c0);
-            const float dk[4] = {dv.x, dv.y, dv.z, dv.w};
-            const float hc[4] = {hv.x, hv.y, hv.z, hv.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(dk[i], hc[j], acc[i][j]);
-            const float d1u = rt[64 + u], d2u = rt[32 + u], h2u = rt[96 + u];
-            const float4 iv = *(const float4 *)(rt + 128);
-            const float et = rt[132];
-            gb1 += d1u;
-            gb2 += d2u;
-            gw3 = fmaf(et, h2u, gw3);
-            gw1[0] = fmaf(d1u, iv.x, gw1[0]);
-            gw1[1] = fmaf(d1u, iv.y, gw1[1]);
-            gw1[2] = fmaf(d1u, iv.z, gw1[2]);
-            gw1[3] = fmaf(d1u, iv.w, gw1[3]);
-            gb3 += et;
-            lsum += rt[133];
+        for (int r = 0; r < 4; ++r) {
+            b1[m][r] = w[kGB1 + 16 * m + 4 * g + r];
+            b2[m][r] = w[kGB2 + 16 * m + 4 * g + r];
+            w3[m][r] = w[kGW3 + 16 * m + 4 * g + r];
         }
+    }
+    const float bias3 = w[kGB3];
+    const float mean = sc[g], dev = sc[4 + g], ymean = sc[8], ydev = sc[9];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 gw2[2][2] = {{zero, zero}, {zero, zero}};   // [units of layer 2][of layer 1]
+    f32x4 g1[2] = {zero, zero};                       // columns 0-3: w1, 4: b1
+    f32x4 g2[2] = {zero, zero};                       // column 4: b2
+    f32x4 g3[2] = {zero, zero};                       // column 5: w3
+    float gb3 = 0.f, lsum = 0.f;
+    for (long long tile = blockIdx.x; tile * 64 < n; tile += gridDim.x) {
+        const long long s = tile * 64 + 16 * wv + u;
+        const bool valid = s < n;
+        const float in = valid ? (feat[g * ld + s] - mean) / dev : 0.f;
+        const float yt = valid ? (feat[4 * ld + s] - ymean) / ydev : 0.f;
+        f32x4 h1[2], h2[2], d1[2], d2[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            h1[m] = mfma16(a1[m], in, b1[m]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h1[m][r] = tanh_fast(h1[m][r]);
+        }
+        float o = 0.f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f32x4 z = b2[m];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z = mfma16(a2[m][k][r], h1[k][r], z);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                h2[m][r] = tanh_fast(z[r]);
+                o = fmaf(w3[m][r], h2[m][r], o);
+            }
+        }
+        o += __shfl_xor(o, 16, 64);
+        o += __shfl_xor(o, 32, 64);
+        const float e = valid ? o + bias3 - yt : 0.f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d2[m][r] = e * w3[m][r] * (1.f - h2[m][r] * h2[m][r]);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f32x4 z = zero;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z = mfma16(at[m][k][r], d2[k][r], z);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d1[m][r] = z[r] * (1.f - h1[m][r] * h1[m][r]);
+        }
+        // transposed through the wave's LDS (rows of a sample)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            *reinterpret_cast<f32x4 *>(&S.h1[u][16 * m + 4 * g]) = h1[m];
+            *reinterpret_cast<f32x4 *>(&S.h2[u][16 * m + 4 * g]) = h2[m];
+            *reinterpret_cast<f32x4 *>(&S.d1[u][16 * m + 4 * g]) = d1[m];
+            *reinterpret_cast<f32x4 *>(&S.d2[u][16 * m + 4 * g]) = d2[m];
+        }
+        S.in[u][g] = in;
+        S.in[u][4 + g] = g == 0 ? 1.f : (g == 1 ? e : 0.f);
+        __syncthreads();   // (every wave runs the same tiles)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int sm = 4 * q + g;   // the sample of this lane's k
+            const float x = u < 5 ? S.in[sm][u] : 0.f;
+            const float one = u == 4 ? 1.f : 0.f, err = u == 5 ? S.in[sm][5] : 0.f;
+            const float hb[2] = {S.h1[sm][u], S.h1[sm][16 + u]};
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const float dk = S.d2[sm][16 * m + u];
+                gw2[m][0] = mfma16(dk, hb[0], gw2[m][0]);
+                gw2[m][1] = mfma16(dk, hb[1], gw2[m][1]);
+                g2[m] = mfma16(dk, one, g2[m]);
+                g1[m] = mfma16(S.d1[sm][16 * m + u], x, g1[m]);
+                g3[m] = mfma16(S.h2[sm][16 * m + u], err, g3[m]);
+            }
+        }
+        gb3 += e;
+        lsum = fmaf(e, e, lsum);
         __syncthreads();
     }
-    float *p = part + (long long)blockIdx.x * kGPart;
+    // the waves' sums through LDS, added in wave order
+    float *p = L.sum[wv];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) p[kGW2 + 32 * (k0 + i) + c0 + j] = acc[i][j];
-    if (l < 32) {
-        p[kGB1 + l] = gb1;
-        p[kGB2 + l] = gb2;
-        p[kGW3 + l] = gw3;
-        for (int j = 0; j < 4; ++j) p[kGW1 + 4 * l + j] = gw1[j];
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * m + 4 * g + r;
+            p[kGW2 + 32 * row + u] = gw2[m][0][r];
+            p[kGW2 + 32 * row + 16 + u] = gw2[m][1][r];
+            if (u < 4) p[kGW1 + 4 * row + u] = g1[m][r];
+            if (u == 4) {
+                p[kGB1 + row] = g1[m][r];
+                p[kGB2 + row] = g2[m][r];
+            }
+            if (u == 5) p[kGW3 + row] = g3[m][r];
+        }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        gb3 += __shfl_xor(gb3, o, 64);
+        lsum += __shfl_xor(lsum, o, 64);
     }
     if (l == 0) {
         p[kGB3] = gb3;
         p[kGuessParams] = lsum;
     }
+    __syncthreads();
+    for (int k = t; k < kGPart; k += 64 * kGWaves)
+        part[(long long)blockIdx.x * kGPart + k] = (L.sum[0][k] + L.sum[1][k]) + (L.sum[2][k] + L.sum[3][k]);
 }
 
 // g_p = gscale * sum over nparts rows of gsrc (row stride `stride`), in a
-// fixed order; optional gradient output, loss accumulation (thread 1249,
-// only when loss_acc is given) and Adam update (Kingma & Ba, Alg. 1, with
-// c1 = 1 - b1^t, c2 = 1 - b2^t)
+// fixed order; optional gradient output, loss (column 1249, only when
+// loss_acc is given: added to it, or stored) and Adam update (Kingma & Ba,
+// Alg. 1, with c1 = 1 - b1^t, c2 = 1 - b2^t).  A workgroup takes 64 columns
+// with 16 threads each, thread group q the rows q, q + 16, ..., eight in
+// flight: a thread per column waited for 128 rows four at a time, 12 us
+// against 4.0 us.
 struct UpdateArgs {
     const float *gsrc;
     int nparts;
@@ -288,28 +352,37 @@ struct UpdateArgs {
     double gscale, lscale;
     float *gout;
     double *loss_acc;
+    int loss_add;
     float *w, *m, *v;
     double lr, b1, b2, eps, c1, c2;
     int adam;
 };
 
-__global__ __launch_bounds__(256) void k_guess_update(UpdateArgs a)
+constexpr int kUCols = 64, kURows = 16;
+
+__global__ __launch_bounds__(kUCols * kURows) void k_guess_update(UpdateArgs a)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > kGuessParams) return;
-    if (p == kGuessParams && !a.loss_acc) return;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int q = 0;
-    for (; q + 4 <= a.nparts; q += 4) {
-        s0 += (double)a.gsrc[(q + 0) * a.stride + p];
-        s1 += (double)a.gsrc[(q + 1) * a.stride + p];
-        s2 += (double)a.gsrc[(q + 2) * a.stride + p];
-        s3 += (double)a.gsrc[(q + 3) * a.stride + p];
+    __shared__ double red[kURows][kUCols];
+    const int c = threadIdx.x % kUCols, r = threadIdx.x / kUCols;
+    const int p = blockIdx.x * kUCols + c;
+    double s = 0.0;
+    if (p <= kGuessParams && (p < kGuessParams || a.loss_acc)) {
+        int q = r;
+        for (; q + 7 * kURows < a.nparts; q += 8 * kURows) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = a.gsrc[(long long)(q + k * kURows) * a.stride + p];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += (double)v[k];
+        }
+        for (; q < a.nparts; q += kURows) s += (double)a.gsrc[(long long)q * a.stride + p];
     }
-    for (; q < a.nparts; ++q) s0 += (double)a.gsrc[q * a.stride + p];
-    const double s = (s0 + s1) + (s2 + s3);
+    red[r][c] = s;
+    __syncthreads();
+    if (r != 0 || p > kGuessParams) return;
+    for (int k = 1; k < kURows; ++k) s += red[k][c];
     if (p == kGuessParams) {
-        *a.loss_acc += s * a.lscale;
+        if (a.loss_acc) *a.loss_acc = (a.loss_add ? *a.loss_acc : 0.0) + s * a.lscale;
         return;
     }
     const double g = s * a.gscale;
@@ -370,7 +443,7 @@ int launch_grad(qsym_guess_trainer *tr, const float *w, const float *feat, long 
                 long long n, int &nparts)
 {
     nparts = (int)std::min<long long>((n + 63) / 64, tr->max_parts);
-    hipLaunchKernelGGL(k_guess_grad, dim3(nparts), dim3(64), 0, tr->stream, w, feat, ld, n,
+    hipLaunchKernelGGL(k_guess_grad, dim3(nparts), dim3(64 * kGWaves), 0, tr->stream, w, feat, ld, n,
                        tr->part);
     TCHK(tr, hipGetLastError());
     return QSYM_OK;
@@ -378,7 +451,7 @@ int launch_grad(qsym_guess_trainer *tr, const float *w, const float *feat, long 
 
 int launch_update(qsym_guess_trainer *tr, const UpdateArgs &a)
 {
-    hipLaunchKernelGGL(k_guess_update, dim3(grid_of(kGuessParams + 1, 256)), dim3(256), 0,
+    hipLaunchKernelGGL(k_guess_update, dim3(grid_of(kGuessParams + 1, kUCols)), dim3(kUCols * kURows), 0,
                        tr->stream, a);
     TCHK(tr, hipGetLastError());
     return QSYM_OK;
@@ -390,7 +463,7 @@ bool bad_state_args(long long n, const void *st, const void *dt) { return n < 0 
 
 // ------------------------------------------------------------------------
 // Scratch of the allocation-free loss gradient (qsym_guess_grad_static):
-// the per-wave partial sums of up to kStaticParts waves (64 samples each)
+// the partial sums of up to kStaticParts workgroups (64 samples each)
 // and the loss accumulator, in one file-scope device array.  Every device
 // the library runs on holds its own copy until the process ends; host code
 // reaches it only through the address hipGetSymbolAddress gives on that
@@ -558,7 +631,6 @@ int qsym_guess_grad(qsym_guess_trainer *tr, const float *weights, const float *f
         return tfail(tr, QSYM_EINVAL, "guess_grad: need 1 <= n <= max_batch, ld >= n");
     int nparts;
     if (int rc = launch_grad(tr, weights, feat, ld, n, nparts)) return rc;
-    hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, tr->stream, tr->loss, 1);
     UpdateArgs a{};
     a.gsrc = tr->part;
     a.nparts = nparts;
@@ -588,13 +660,11 @@ int qsym_guess_grad_static(const float *weights, const float *feat, int64_t ld, 
     float *part = (float *)base;
     double *lacc = (double *)((char *)base + kStaticPartBytes);
     hipStream_t st = (hipStream_t)stream;
-    // the same launches as qsym_guess_grad: one wave per 64 samples (every
-    // partial row is written whole), the loss accumulator cleared by a kernel
+    // the same launches as qsym_guess_grad: one workgroup per 64 samples (every
+    // partial row is written whole); the update stores the loss
     const int nparts = (int)((n + 63) / 64);
-    hipLaunchKernelGGL(k_guess_grad, dim3(nparts), dim3(64), 0, st, weights, feat, (long long)ld,
-                       (long long)n, part);
-    if (hipGetLastError() != hipSuccess) return QSYM_EHIP;
-    hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, st, lacc, 1);
+    hipLaunchKernelGGL(k_guess_grad, dim3(nparts), dim3(64 * kGWaves), 0, st, weights, feat,
+                       (long long)ld, (long long)n, part);
     if (hipGetLastError() != hipSuccess) return QSYM_EHIP;
     UpdateArgs a{};
     a.gsrc = part;
@@ -604,7 +674,8 @@ int qsym_guess_grad_static(const float *weights, const float *feat, int64_t ld, 
     a.lscale = 1.0 / (double)n;
     a.gout = grad;
     a.loss_acc = lacc;
-    hipLaunchKernelGGL(k_guess_update, dim3(grid_of(kGuessParams + 1, 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_guess_update, dim3(grid_of(kGuessParams + 1, kUCols)), dim3(kUCols * kURows),
+                       0, st, a);
     if (hipGetLastError() != hipSuccess) return QSYM_EHIP;
     if (loss) {
         if (hipMemcpyAsync(loss, lacc, sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -667,6 +738,7 @@ int qsym_guess_train(qsym_guess_trainer *tr, float *weights, const float *feat, 
             a.gscale = 2.0 / (double)nb;
             a.lscale = 1.0 / (double)n;
             a.loss_acc = tr->curve + e;
+            a.loss_add = 1;
             a.w = weights;
             a.m = tr->m;
             a.v = tr->v;

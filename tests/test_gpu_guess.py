@@ -153,6 +153,39 @@ def test_gradient_matches_oracle_backprop(Q, orc, n):
     tr.close()
 
 
+@pytest.mark.parametrize("n,ld", [(1, 1), (15, 20), (16, 16), (17, 40), (63, 64), (65, 65), (129, 140),
+                                  (8193, 8200), (262209, 262209)])
+@pytest.mark.parametrize("scale_w", [0.3, 3.0])
+def test_gradient_tile_edges(Q, orc, n, ld, scale_w):
+    """The gradient at the edges of a wave's 16 and a workgroup's 64 samples,
+    rows longer than the samples (the rest holds NaN), gentle and saturated
+    networks, more tiles than partial rows (262,209 samples), against the FP64
+    backprop to 1e-4 of each block's largest entry; a second trainer gives
+    the same bits."""
+    import torch
+    say(f"guess_grad edges n={n} ld={ld} weights {scale_w}")
+    tr, feat, F_o, y_o = _both_datasets(Q, orc, n, 61)
+    w = _rand_weights(56)
+    w[:NP] = (w[:NP] / 0.3 * scale_w).astype(np.float32)
+    wt = torch.from_numpy(w.astype(np.float32)).cuda()
+    wide = torch.full((5, ld), float("nan"), dtype=torch.float32, device="cuda")
+    wide[:, :n] = feat[:, :n]
+    f64 = feat[:, :n].cpu().numpy().astype(np.float64)
+    g, loss = tr.grad(wt, wide, n=n)
+    loss_o, g_o = orc.guess_loss_grad(w, np.ascontiguousarray(f64[:4].T), f64[4])
+    g = g.cpu().numpy()
+    scale = np.abs(g_o).max()
+    for lo, hi in ((0, 128), (128, 160), (160, 1184), (1184, 1216), (1216, 1248), (1248, 1249)):
+        blk = np.abs(g_o[lo:hi]).max()
+        assert np.abs(g[lo:hi] - g_o[lo:hi]).max() <= 1e-4 * max(blk, 1e-2 * scale), (lo, hi)
+    assert loss == pytest.approx(loss_o, rel=1e-5)
+    tr.close()
+    tr2 = Q.GuessTrainer(n)
+    g2, loss2 = tr2.grad(wt, wide, n=n)
+    assert np.array_equal(g2.cpu().numpy(), g) and loss2 == loss
+    tr2.close()
+
+
 def test_adam_matches_oracle(Q, orc):
     import torch
     rng = np.random.Generator(np.random.PCG64(57))
