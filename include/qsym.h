@@ -159,13 +159,13 @@ int qsym_set_state(qsym_ctx *ctx, const double *m, const double *h, const double
                    const double *v, int32_t where);
 int qsym_get_state(qsym_ctx *ctx, double *q, double *v, int32_t where);
 
-/* nsteps hybrid steps of size tau (Sec. 2.3).  Asynchronous: the first call
- * for a given tau captures the step into HIP graphs that are replayed: the
- * step's body with the drift that ends it and begins the next (one launch;
- * the same additions in the same order as two), and the body with the last
- * drift, so a call is one drift launch and nsteps graph launches.  The
- * result does not depend on how steps are split over calls.  A negative
- * tau integrates backwards (used with a_E = 0). */
+/* nsteps hybrid steps of size tau (Sec. 2.3).  Asynchronous.  Systems of at
+ * most 256 bodies take up to 256 steps in one launch; otherwise a call is the
+ * first drift, then per step its kernels and one launch of the drift that
+ * ends it and begins the next (the same additions in the same order as two).
+ * Small contexts replay HIP graphs of several steps, captured once 64 steps
+ * of one tau were taken.  The result does not depend on how steps are split
+ * over calls.  A negative tau integrates backwards (used with a_E = 0). */
 int qsym_step(qsym_ctx *ctx, double tau, int64_t nsteps);
 /* nsteps encounter-free steps with the Keplerian and interaction operators
  * swapped (Sec. 2, after the second-order composition: without the

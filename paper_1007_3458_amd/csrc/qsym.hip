@@ -1,5 +1,5 @@
 // qsym.hip -- host side of the MI355X DH hybrid-step library: workspace
-// layout, work tables, kernel launches, HIP-graph capture of one step, the
+// layout, work tables, kernel launches, HIP graphs of several steps, the
 // kick autotuner and the C ABI declared in include/qsym.h.
 #include "qsym.h"
 
@@ -338,15 +338,16 @@ struct qsym_ctx {
     int nitems[2] = {0, 0};
     int grid_kick[2] = {0, 0};
     Tables T;
-    // captured steps: [kind] a step's body and the drift fused with the
-    // next step's first, [2 + kind] a step's body and its last drift (kind
-    // 0 hybrid, 1 the encounter-free swapped step)
+    // captured steps per kind (0 hybrid, 1 the encounter-free swapped step):
+    // kGraphSteps times a step's body and the drift fused with the next
+    // step's first, captured once kGraphAfter steps of this tau were taken
     struct StepGraph {
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         double tau = 0.0;
+        int64_t seen = 0;   // steps of this tau
         bool valid = false;
-    } g[4];
+    } g[2];
     int profile = 0;   // 1: kernel timings, 2: and workgroup records
     // profiling: event pairs recorded around launches without waiting; the
     // pending pairs are read (and the events recycled) at the next flush
@@ -1133,8 +1134,8 @@ hipError_t enqueue_step_body(qsym_ctx *c, double tau, hipStream_t st)
     return run_apply(c, half, 0.0, 1, 0, 0, 1, st, P_APPLY2, 0);
 }
 
-// body + the fused drift between this step and the next (graph of the steps
-// before a call's last), body + the last drift (graph of its last step)
+// body + the fused drift between this step and the next (the steps before a
+// call's last), body + the last drift (its last step)
 hipError_t enqueue_step_mid(qsym_ctx *c, double tau, hipStream_t st)
 {
     hipError_t e = enqueue_step_body(c, tau, st);
@@ -1334,8 +1335,11 @@ hipError_t run_small(qsym_ctx *c, double tau, int64_t nsteps, int kind)
     return hipSuccess;
 }
 
-// nsteps steps of one kind (0 hybrid, 1 swapped): eager launches in
-// profiling mode, else one captured step replayed
+constexpr int kGraphSteps = 8;     // steps of one graph
+constexpr int kGraphAfter = 64;    // steps of one tau before its graph is made
+constexpr long long kGraphBodies = 8192;   // contexts of fewer bodies use graphs
+
+// nsteps steps of one kind (0 hybrid, 1 swapped)
 int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
 {
     if (!c || nsteps < 0 || !std::isfinite(tau)) return fail(c, QSYM_EINVAL, "step: bad argument");
@@ -1357,22 +1361,31 @@ int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
         return kind == 0 ? enqueue_first_drift(c, tau, c->stream, 0)
                          : enqueue_swapped_first_drift(c, tau, c->stream, 0);
     };
-    if (c->profile) {
-        HIPCHK(c, first());
-        for (int64_t k = 0; k < nsteps; ++k) HIPCHK(c, (k + 1 < nsteps ? mid : last)(c, tau, c->stream));
-        leave(c);
-        return QSYM_OK;
+    // Launched one by one, or, below kGraphBodies, in graphs of kGraphSteps
+    // steps.  The device waits some 20 us between two graphs, more than the
+    // host takes to launch a step's kernels, so a graph holds several steps;
+    // and it costs 22 us a node to capture and instantiate, so it is made once
+    // the steps already taken with this tau would have paid for it.
+    // Intervals of 20 steps as graphs of one step, one by one, and as graphs
+    // of eight, in us: 1024 bodies 1868, 1852, 1770; 4100: 2455, 2407, 2351;
+    // 16,388: 7197, 7086, 7103; 8 steps of the 512-system batch 17,580,
+    // 17,530, 17,970; first interval of a context, 1024 bodies: 2459, 2080.
+    auto &G = c->g[kind];
+    if (G.tau != tau) {
+        G.tau = tau;
+        G.seen = 0;
+        G.valid = false;
     }
-    // captured once per tau and kind: [body + fused drift], [body + last drift]
-    auto graph = [&](int slot, Enq enqueue) -> int {
-        auto &G = c->g[slot];
-        if (G.valid && G.tau == tau) return QSYM_OK;
+    const int64_t mids = nsteps - 1;
+    const bool graphs = !c->profile && c->ntot < kGraphBodies;
+    if (graphs && !G.valid && G.seen >= kGraphAfter && mids >= kGraphSteps) {
         if (G.exec) { hipGraphExecDestroy(G.exec); G.exec = nullptr; }
         if (G.graph) { hipGraphDestroy(G.graph); G.graph = nullptr; }
         HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-        hipError_t e = enqueue(c, tau, c->stream);
+        hipError_t e = hipSuccess;
+        for (int k = 0; k < kGraphSteps && e == hipSuccess; ++k) e = mid(c, tau, c->stream);
         hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(c->stream, &g);
+        const hipError_t e2 = hipStreamEndCapture(c->stream, &g);
         if (e != hipSuccess || e2 != hipSuccess) {
             if (g) hipGraphDestroy(g);
             return fail(c, QSYM_EHIP, std::string("graph capture: ") +
@@ -1380,16 +1393,15 @@ int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
         }
         G.graph = g;
         HIPCHK(c, hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0));
-        G.tau = tau;
         G.valid = true;
-        return QSYM_OK;
-    };
-    int rc;
-    if (nsteps > 1 && (rc = graph(kind, mid)) != QSYM_OK) return rc;
-    if ((rc = graph(2 + kind, last)) != QSYM_OK) return rc;
+    }
     HIPCHK(c, first());
-    for (int64_t k = 0; k + 1 < nsteps; ++k) HIPCHK(c, hipGraphLaunch(c->g[kind].exec, c->stream));
-    HIPCHK(c, hipGraphLaunch(c->g[2 + kind].exec, c->stream));
+    int64_t k = 0;
+    if (graphs && G.valid)
+        for (; mids - k >= kGraphSteps; k += kGraphSteps) HIPCHK(c, hipGraphLaunch(G.exec, c->stream));
+    for (; k < mids; ++k) HIPCHK(c, mid(c, tau, c->stream));
+    HIPCHK(c, last(c, tau, c->stream));
+    G.seen += nsteps;
     leave(c);
     return QSYM_OK;
 }
