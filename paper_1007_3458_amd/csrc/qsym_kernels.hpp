@@ -2382,6 +2382,7 @@ __device__ __forceinline__ double &hw_at(const Dev &d, int f, int k)
 
 struct SetLds {
     double *x, *y, *z, *u, *v, *w, *m;
+    double *r = nullptr;   // [6][kCoopMin], workgroup sets only
 };
 
 // the state a set is integrated in: the snapshot (q0, v0) it starts from and
@@ -2511,10 +2512,9 @@ __device__ void set_pair_acc(const SetLds &S, int n, int a, int l, int L, double
 // 27 pairs hold about six inside.  So each lane first marks its pairs
 // inside (32 at a time, a bit each) and then takes only those, in the same
 // ascending order and with the same arithmetic as a loop over all of them.
-__device__ void herm_pairs(const SetLds &S, int n, int a, int l, int L, double G, double rc,
-                           double eps, double acc[3], double jrk[3])
+__device__ void herm_pairs(const SetLds &S, int n, int a, int l, int L, double G,
+                           const TransConst &tc, double eps, double acc[3], double jrk[3])
 {
-    const TransConst tc = trans_const(rc);
     const double X0 = S.x[a], X1 = S.y[a], X2 = S.z[a];
     const double U0 = S.u[a], U1 = S.v[a], U2 = S.w[a];
     const double eps2 = eps * eps;
@@ -2702,7 +2702,8 @@ __device__ void hermite_set_wave(const HermArgs &a, const HermState &d, const He
     wave_lds_sync();
     // initial force and first step
     double hloc = INFINITY;
-    herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, A, J);
+    const TransConst tc = trans_const(rc);
+    herm_pairs(S, n, kk, l, L, a.G, tc, a.epsH, A, J);
     group_sum6(A, J, L);
     herm_central(X, U, mu, A, J);
     {
@@ -2734,7 +2735,7 @@ __device__ void hermite_set_wave(const HermArgs &a, const HermState &d, const He
         }
         wave_lds_sync();
         double a1[3], j1[3];
-        herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, a1, j1);
+        herm_pairs(S, n, kk, l, L, a.G, tc, a.epsH, a1, j1);
         group_sum6(a1, j1, L);
         herm_central(xp, up, mu, a1, j1);
         const double hb = herm_correct(hk, a.eta, a1, j1, xp, up, X, U, A, J);
@@ -2781,12 +2782,19 @@ __device__ __forceinline__ double block_min_waves(double v, double *red)
     return wave_uniform(r);
 }
 
-// One set of kWaveMax < n <= kHermThreads members on one workgroup: member
-// k on the L lanes of group k (L the largest power of two <= 64 with
-// L n <= kHermThreads, so no group holds two members), its state (X, U, A,
-// J) in registers of those lanes, the staged set in LDS.  Same steps and
-// arithmetic as hermite_set_wave; per substep three barriers: the staged
-// prediction written, read, and the step-size minimum.
+// One set of kWaveMax < n <= kCoopMin members on one workgroup.  The pair sums
+// run on all lanes: member k's on the L lanes of group k (L the largest power
+// of two <= 64 with L n <= kHermThreads, so no group holds two members).  All
+// else of a substep (central force, corrector, step criterion, predictor)
+// runs once a member, on thread k, which keeps the member's state (X, U, A, J)
+// in registers: a wave holds 64 members there, where lane groups made every
+// wave of the workgroup issue those some 330 instructions, two waves to a
+// SIMD, and took the step's minimum through LDS.  Sums and staged state pass
+// through LDS; two barriers a substep (three above 64 members, whose minimum
+// spans waves).  Same steps and arithmetic as hermite_set_wave.  Bound by the
+// chain of one substep: a predictor, the pair sums (half of it) and a
+// corrector.  k_hermite, mean of a step of three 512-system batches:
+// 648 -> 584 us; of three 131,076-body disks: 408 -> 391 us.
 __device__ void hermite_set_block(const HermArgs &a, const HermState &d, const HermSet &hs,
                                   const SetLds &S, double *red, int &nsub_out, int &fail_out)
 {
@@ -2796,99 +2804,145 @@ __device__ void hermite_set_block(const HermArgs &a, const HermState &d, const H
     int L = 1;
     while (L < 64 && 2 * L * n <= kHermThreads) L <<= 1;
     const int k = t / L, l = t % L;
-    const bool mine = k < n;
-    const int kk = mine ? k : 0;   // idle groups shadow member 0; their results are dropped
-    const int i = hs.mem[kk];
+    const bool pairs = k < n;                 // this lane belongs to a pair group
+    const int kp = pairs ? k : 0;
+    // member waves (uniform), this thread's member; their idle lanes shadow
+    // member 0 and their results are dropped
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool mwave = 64 * wave < n;
+    const bool mine = t < n;
+    const int i = hs.mem[mine ? t : 0];
+    const int kk = mine ? t : 0;
     const double mu = hs.mu;
     const double half = a.tau / 2.0;
-    double X[3] = {d.x0[i], d.y0[i], d.z0[i]};
-    if (mine && l == 0) {
-        S.x[k] = X[0];
-        S.y[k] = X[1];
-        S.z[k] = X[2];
-        S.m[k] = d.m[i];
-    }
+    const bool many = n > 64;
+    double *const R = S.r;                    // [6][kCoopMin] sums of the lane groups
+    double X[3], U[3], A[3], J[3];
+    auto stage = [&](double *x, double *y, double *z, const double v[3]) {
+        if (mine) {
+            x[t] = v[0];
+            y[t] = v[1];
+            z[t] = v[2];
+        }
+    };
+    auto give = [&](const double *v, int m) {
+        if (pairs && l == 0)
+            for (int c = 0; c < m; ++c) R[c * kCoopMin + k] = v[c];
+    };
+    X[0] = d.x0[i];
+    X[1] = d.y0[i];
+    X[2] = d.z0[i];
+    if (mine) S.m[t] = d.m[i];
+    stage(S.x, S.y, S.z, X);
     __syncthreads();
     // step 5: v0 -= tau/2 * sum W-weighted in-set forces at q0
-    double U[3], A[3], J[3];
     {
         double acc[3];
-        set_pair_acc(S, n, kk, l, L, a.G, rc, acc);
+        set_pair_acc(S, n, kp, l, L, a.G, rc, acc);
         group_sum3(acc, L);
-        U[0] = d.vx0[i] - half * acc[0];
-        U[1] = d.vy0[i] - half * acc[1];
-        U[2] = d.vz0[i] - half * acc[2];
-    }
-    if (mine && l == 0) {
-        S.u[k] = U[0];
-        S.v[k] = U[1];
-        S.w[k] = U[2];
+        give(acc, 3);
     }
     __syncthreads();
+    U[0] = d.vx0[i] - half * R[kk];
+    U[1] = d.vy0[i] - half * R[kCoopMin + kk];
+    U[2] = d.vz0[i] - half * R[2 * kCoopMin + kk];
+    stage(S.u, S.v, S.w, U);
+    __syncthreads();
+    const TransConst tc = trans_const(rc);
+    auto forces = [&]() {
+        double f[6];
+        herm_pairs(S, n, kp, l, L, a.G, tc, a.epsH, f, f + 3);
+        group_sum6(f, f + 3, L);
+        give(f, 6);
+        __syncthreads();
+    };
+    auto take = [&](double acc[3], double jrk[3]) {
+        for (int c = 0; c < 3; ++c) {
+            acc[c] = R[c * kCoopMin + kk];
+            jrk[c] = R[(3 + c) * kCoopMin + kk];
+        }
+    };
+    // the smallest step of the members, on the member waves
+    auto smallest = [&](double hb) {
+        double v = mwave ? wave_min((mine && hb > 0.0) ? hb : INFINITY) : INFINITY;
+        if (many) {
+            if (mwave && (t & 63) == 0) red[wave] = v;
+            __syncthreads();
+            v = red[0];
+            for (int w = 1; 64 * w < n; ++w) v = fmin(v, red[w]);
+        }
+        return wave_uniform(v);
+    };
     // initial force and first step
-    herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, A, J);
-    group_sum6(A, J, L);
-    herm_central(X, U, mu, A, J);
-    double hloc = INFINITY;
-    {
-        const double hb = a.eta_s * dnorm3(A[0], A[1], A[2]) / dnorm3(J[0], J[1], J[2]);
-        if (mine && hb > 0.0) hloc = hb;
+    forces();
+    double hb = INFINITY;
+    if (mwave) {
+        take(A, J);
+        herm_central(X, U, mu, A, J);
+        hb = a.eta_s * dnorm3(A[0], A[1], A[2]) / dnorm3(J[0], J[1], J[2]);
     }
-    double h = block_min_waves<kHermThreads>(hloc, red);
+    double h = smallest(hb);
     const double sgn = a.tau >= 0.0 ? 1.0 : -1.0;
     const double T = fabs(a.tau);
     double tt = 0.0;
     int nsub = 0, fail = 0;
     bool last = (T == 0.0);
-    while (!last) {
-        if (nsub >= a.max_substeps) {
-            fail = 1;
-            break;
-        }
-        if (!(h > 0.0) || h >= T - tt) {
-            h = T - tt;
-            last = true;
-        }
-        const HermStep hk = herm_step(sgn * h);
+    int *const go = reinterpret_cast<int *>(red + kHermThreads / 64);   // another substep follows
+    for (;;) {
+        HermStep hk{};
         double xp[3], up[3];
-        herm_predict(hk, X, U, A, J, xp, up);
-        __syncthreads();   // every lane is done reading the previous state (and red)
-        if (mine && l == 0) {
-            S.x[k] = xp[0]; S.y[k] = xp[1]; S.z[k] = xp[2];
-            S.u[k] = up[0]; S.v[k] = up[1]; S.w[k] = up[2];
+        if (mwave) {
+            bool more = !last;
+            if (more && nsub >= a.max_substeps) {
+                fail = 1;
+                more = false;
+            }
+            if (more) {
+                if (!(h > 0.0) || h >= T - tt) {
+                    h = T - tt;
+                    last = true;
+                }
+                hk = herm_step(sgn * h);
+                herm_predict(hk, X, U, A, J, xp, up);
+                stage(S.x, S.y, S.z, xp);
+                stage(S.u, S.v, S.w, up);
+            }
+            if (t == 0) *go = more ? 1 : 0;
         }
         __syncthreads();
-        double a1[3], j1[3];
-        herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, a1, j1);
-        group_sum6(a1, j1, L);
-        herm_central(xp, up, mu, a1, j1);
-        const double hb = herm_correct(hk, a.eta, a1, j1, xp, up, X, U, A, J);
-        tt += h;
+        if (!__builtin_amdgcn_readfirstlane(*go)) break;
+        forces();
+        if (mwave) {
+            double a1[3], j1[3];
+            take(a1, j1);
+            herm_central(xp, up, mu, a1, j1);
+            hb = herm_correct(hk, a.eta, a1, j1, xp, up, X, U, A, J);
+            tt += h;
+        }
         ++nsub;
-        h = block_min_waves<kHermThreads>((mine && hb > 0.0) ? hb : INFINITY, red);
+        h = smallest(hb);
     }
     // step 7: v1 -= tau/2 * W-weighted in-set forces at q1, write back
+    stage(S.x, S.y, S.z, X);
     __syncthreads();
-    if (mine && l == 0) {
-        S.x[k] = X[0];
-        S.y[k] = X[1];
-        S.z[k] = X[2];
+    {
+        double acc[3];
+        set_pair_acc(S, n, kp, l, L, a.G, rc, acc);
+        group_sum3(acc, L);
+        give(acc, 3);
     }
     __syncthreads();
-    double acc[3];
-    set_pair_acc(S, n, kk, l, L, a.G, rc, acc);
-    group_sum3(acc, L);
-    if (mine && l == 0) {
+    if (mine) {
         d.x[i] = X[0];
         d.y[i] = X[1];
         d.z[i] = X[2];
-        d.vx[i] = U[0] - half * acc[0];
-        d.vy[i] = U[1] - half * acc[1];
-        d.vz[i] = U[2] - half * acc[2];
+        d.vx[i] = U[0] - half * R[t];
+        d.vy[i] = U[1] - half * R[kCoopMin + t];
+        d.vz[i] = U[2] - half * R[2 * kCoopMin + t];
     }
     __syncthreads();   // the staging arrays are reused by the next set
     nsub_out = nsub;
-    fail_out = fail;
+    fail_out = fail;   // (of the member waves; the caller takes thread 0's)
 }
 
 template <int NT>
@@ -2914,7 +2968,8 @@ __global__ __launch_bounds__(kHermThreads) void k_hermite(HermArgs a)
     const Dev &d = a.d;
     __shared__ double s_x[kHermLds], s_y[kHermLds], s_z[kHermLds];
     __shared__ double s_u[kHermLds], s_v[kHermLds], s_w[kHermLds], s_m[kHermLds];
-    __shared__ double lds[kHermThreads / 64];
+    __shared__ double s_r[6 * kCoopMin];
+    __shared__ double lds[kHermThreads / 64 + 1];
     const int t = threadIdx.x;
     wg_start(a.rec);
     const int nwg = gridDim.x, wpb = kHermThreads / 64;
@@ -2931,7 +2986,8 @@ __global__ __launch_bounds__(kHermThreads) void k_hermite(HermArgs a)
         if (d.set_count[sidx] > kCoopMin) continue;   // the grid phase takes it
         int nsub, fail;
         hermite_set_block(a, herm_state(d), herm_set(d, a.G, sidx),
-                          SetLds{s_x, s_y, s_z, s_u, s_v, s_w, s_m}, lds, nsub, fail);
+                          SetLds{s_x, s_y, s_z, s_u, s_v, s_w, s_m, s_r},
+                          lds, nsub, fail);
         if (t == 0) {
             nsub_b += nsub;
             fail_b |= fail;
@@ -3062,6 +3118,7 @@ __device__ void hermite_grid_sets(const HermArgs &a, double *red, int *s_ok)
         if (n <= kCoopMin) continue;
         const int b0 = d.set_start[sidx];
         const double rc = d.set_rc[sidx];
+        const TransConst tc = trans_const(rc);
         double *gs = d.hw + (long long)HS * fs + b0;
         const SetLds S{gs, gs + fs, gs + 2 * fs, gs + 3 * fs, gs + 4 * fs, gs + 5 * fs, gs + 6 * fs};
         int L = 1;
@@ -3109,7 +3166,7 @@ __device__ void hermite_grid_sets(const HermArgs &a, double *red, int *s_ok)
             const int k = k0 + g;
             const int kk = k < n ? k : 0;
             double acc[3], jr[3];
-            herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, acc, jr);
+            herm_pairs(S, n, kk, l, L, a.G, tc, a.epsH, acc, jr);
             group_sum6(acc, jr, L);
             if (k < n && l == 0) {
                 const double X[3] = {S.x[k], S.y[k], S.z[k]}, U[3] = {S.u[k], S.v[k], S.w[k]};
@@ -3168,7 +3225,7 @@ __device__ void hermite_grid_sets(const HermArgs &a, double *red, int *s_ok)
                 const int k = k0 + g;
                 const int kk = k < n ? k : 0;
                 double a1[3], j1[3];
-                herm_pairs(S, n, kk, l, L, a.G, rc, a.epsH, a1, j1);
+                herm_pairs(S, n, kk, l, L, a.G, tc, a.epsH, a1, j1);
                 group_sum6(a1, j1, L);
                 if (k < n && l == 0) {
                     const double xp[3] = {S.x[k], S.y[k], S.z[k]}, up[3] = {S.u[k], S.v[k], S.w[k]};

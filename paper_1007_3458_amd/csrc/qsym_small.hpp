@@ -89,7 +89,8 @@ struct SmallLds {
     // Hermite staging
     double hx[kHermLds], hy[kHermLds], hz[kHermLds], hu[kHermLds], hv[kHermLds], hw[kHermLds],
         hm[kHermLds], hpad[kHermLds];   // (hpad: the kick's tile, 8 kHermLds doubles from hx on)
-    double red[kHermThreads / 64];
+    double hr[6 * kCoopMin];
+    double red[kHermThreads / 64 + 1];
     unsigned hist[kHist];
     unsigned long long kit;
     unsigned kmax, krs;
@@ -488,8 +489,8 @@ __device__ __forceinline__ void small_hermite(SmallLds &L, const SmallArgs &a, d
     for (int s = 0; s < nsets; ++s) {
         if (__builtin_amdgcn_readfirstlane(L.scount[s]) <= kWaveMax) continue;
         int nsub, fail;
-        hermite_set_block(a.h, hs, set_of(s), SetLds{L.hx, L.hy, L.hz, L.hu, L.hv, L.hw, L.hm}, L.red,
-                          nsub, fail);
+        hermite_set_block(a.h, hs, set_of(s),
+                          SetLds{L.hx, L.hy, L.hz, L.hu, L.hv, L.hw, L.hm, L.hr}, L.red, nsub, fail);
         nsub_b += nsub;
         fail_b |= fail;
     }
