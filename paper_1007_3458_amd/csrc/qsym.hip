@@ -54,7 +54,7 @@ struct Layout {
     size_t off_swcnt = 0, off_swslot = 0, off_swrec = 0, off_swlarge = 0, off_syssw = 0,
            off_swpart = 0;
     long long sw_nb = 1;       // grid-sweep buckets
-    size_t off_hw = 0, off_ctr = 0, off_kstat = 0, off_E = 0, off_guess = 0;
+    size_t off_hw = 0, off_ctr = 0, off_kstat = 0, off_guess = 0;
     size_t off_small = 0;      // counters and figures of k_small_steps
     bool small = false;        // every system has at most kSmallMax bodies
     size_t off_erec = 0, off_ewcol = 0, off_ewrec = 0, off_sysu0 = 0, off_sysr0 = 0;
@@ -98,8 +98,10 @@ long long sys_enc_cap(long long n)
 
 // energy pair sum: units of 128 i x 64 j over each system's upper triangle
 // (row b, i in [128 b, 128 b + 128), meets the 64-blocks of j from 2 b on),
-// 64 columns each; at least 4 units per wave where the work allows, at most
-// 4096 waves (16 per compute unit)
+// 64 columns each; at least 16 columns per wave where the work allows, at most
+// 4096 waves (16 per compute unit).  A column is a chain of some 100 cycles;
+// k_energy_pairs with 256 of them a wave (4 units) and with 16: 8 systems of 4
+// bodies 25.8, 7.6 us; 1024 bodies 31.4, 8.5; 4100: 34.8, 12.5.
 long long energy_units(long long n)
 {
     const long long nj = (n + 63) / 64, ni = (n + 127) / 128;
@@ -110,7 +112,7 @@ int energy_waves(const std::vector<long long> &off)
 {
     long long units = 0;
     for (size_t s = 0; s + 1 < off.size(); ++s) units += energy_units(off[s + 1] - off[s]);
-    const long long w = std::max<long long>(1, std::min<long long>((units + 3) / 4, 4096));
+    const long long w = std::max<long long>(1, std::min<long long>(4 * units, 4096));
     return (int)((w + 3) / 4 * 4);
 }
 
@@ -239,7 +241,6 @@ Layout make_layout(const qsym_params &p, const std::vector<long long> &off)
     take(L.off_ewrec, (size_t)L.e_waves * sizeof(int));
     take(L.off_sysu0, (size_t)(nsys + 1) * sizeof(long long));
     take(L.off_sysr0, (size_t)(nsys + 1) * sizeof(int));
-    take(L.off_E, (size_t)std::max(nsys, 1) * D);
     take(L.off_guess, (size_t)(kGuessWeights + 5) * sizeof(float));
     L.total = align_up(o, 256);
     return L;
@@ -315,7 +316,6 @@ Dev bind(char *base, const Layout &L)
     d.e_wrec = (int *)(base + L.off_ewrec);
     d.sys_u0 = (long long *)(base + L.off_sysu0);
     d.sys_r0 = (int *)(base + L.off_sysr0);
-    d.E = (double *)(base + L.off_E);
     d.guess = (float *)(base + L.off_guess);
     return d;
 }
@@ -371,6 +371,10 @@ struct qsym_ctx {
     int cus = 256;           // the device's compute units
     int apply_parts = 1;     // threads per body of the partial-sum reduction (1 or 4)
     double tau_crude = 0.0;  // |tau| of the crude sweep being enqueued
+    int device = 0;
+    // host memory that a blocking call's last kernel writes its results to
+    // (the status, then each system's energy), so that they need no copy
+    unsigned long long *result = nullptr;
     std::string err;
 };
 
@@ -1246,6 +1250,48 @@ int sync_status(qsym_ctx *c)
     return status_code(c, h[C_STATUS]);
 }
 
+// Whether one kernel may move a state from or to the caller's arrays of
+// `bytes` each in place of a copy per coordinate: every array lies inside one
+// allocation of this device's memory (a copy takes memory of any kind and
+// refuses to run over an allocation's end), is aligned for its doubles and
+// outside this workspace, and no two written arrays overlap.  The copies,
+// which run one after another, give the same bits wherever both may run.
+// set_state and get_state of 104 bodies: 88 -> 32 and 89 -> 33 us a call.
+struct Span {
+    const void *p;
+    size_t bytes;
+};
+
+bool apart(const Span &a, const Span &b)
+{
+    const char *x = (const char *)a.p, *y = (const char *)b.p;
+    return x + a.bytes <= y || y + b.bytes <= x;
+}
+
+bool one_kernel_moves(qsym_ctx *c, const Span *s, int count, bool written)
+{
+    const Span ws{c->base, c->L.total};
+    for (int k = 0; k < count; ++k) {
+        if (!s[k].p) continue;
+        hipPointerAttribute_t at{};
+        hipDeviceptr_t start = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&at, s[k].p) != hipSuccess ||
+            hipMemGetAddressRange(&start, &size, (hipDeviceptr_t)s[k].p) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        const char *p = (const char *)s[k].p;
+        if (at.type != hipMemoryTypeDevice || at.device != c->device || at.isManaged ||
+            (uintptr_t)p % sizeof(double) || p < (const char *)start ||
+            p + s[k].bytes > (const char *)start + size || !apart(s[k], ws))
+            return false;
+        for (int j = 0; written && j < k; ++j)
+            if (s[j].p && !apart(s[j], s[k])) return false;
+    }
+    return true;
+}
+
 // Encounter-free step with the Keplerian and interaction operators swapped
 // (Sec. 2, after the composition): E_Dft(tau/2) E_Kep(tau/2) E_Int(tau)
 // E_Kep(tau/2) E_Dft(tau/2); one all-pairs kick per step.  The kick and the
@@ -1452,6 +1498,7 @@ int qsym_create(const qsym_params *p, int32_t nsys, const int64_t *offsets, cons
         const hipError_t e = hipGetLastError();
         g_noctx_err = std::string("qsym_create: ") + what + ": " + hipGetErrorString(e);
         if (c->stream) (void)hipStreamDestroy(c->stream);
+        if (c->result) (void)hipHostFree(c->result);
         delete c;
         return code;
     };
@@ -1470,7 +1517,10 @@ int qsym_create(const qsym_params *p, int32_t nsys, const int64_t *offsets, cons
             return bail(QSYM_EHIP, "k_hermite does not fit a compute unit");
         c->grid_blocks = std::max(1, std::min(cus, kGridMax));
         c->cus = std::max(1, cus);
+        c->device = dev;
     }
+    if (hipHostMalloc((void **)&c->result, sizeof(unsigned long long) * (size_t)(1 + nsys)) != hipSuccess)
+        return bail(QSYM_EHIP, "hipHostMalloc");
     if (hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming) != hipSuccess)
         return bail(QSYM_EHIP, "hipEventCreateWithFlags");
     if (hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming) != hipSuccess)
@@ -1544,6 +1594,7 @@ void qsym_destroy(qsym_ctx *c)
     if (c->ev_in) hipEventDestroy(c->ev_in);
     if (c->ev_out) hipEventDestroy(c->ev_out);
     if (c->stream) hipStreamDestroy(c->stream);
+    if (c->result) hipHostFree(c->result);
     delete c;
 }
 
@@ -1557,6 +1608,15 @@ int qsym_set_state(qsym_ctx *c, const double *m, const double *h, const double *
     enter(c);
     hipStream_t st = c->stream;
     const size_t B = sizeof(double) * (size_t)n;
+    const Span in[4] = {{m, B}, {h, B}, {q, 3 * B}, {v, 3 * B}};
+    if (n > 0 && where == QSYM_DEVICE && one_kernel_moves(c, in, 4, false)) {
+        Timer tm(c, P_MOMENTUM);
+        const LoadArgs a{c->d, m, h, q, v, n};
+        hipLaunchKernelGGL(k_load_state, dim3(nblocks_chunks(c)), dim3(kChunk), 0, st, a);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipStreamSynchronize(st));   // nothing is left for the caller's stream to wait for
+        return QSYM_OK;
+    }
     if (n > 0) {
         HIPCHK(c, hipMemcpyAsync(c->d.m, m, B, kind, st));
         HIPCHK(c, hipMemcpyAsync(c->d.h, h, B, kind, st));
@@ -1584,6 +1644,15 @@ int qsym_get_state(qsym_ctx *c, double *q, double *v, int32_t where)
     enter(c);
     hipStream_t st = c->stream;
     const size_t B = sizeof(double) * (size_t)n;
+    const Span out[2] = {{q, 3 * B}, {v, 3 * B}};
+    if (n > 0 && where == QSYM_DEVICE && one_kernel_moves(c, out, 2, true)) {
+        const StoreArgs a{c->d, q, v, n, c->result};
+        hipLaunchKernelGGL(k_store_state, dim3((unsigned)((n + kChunk - 1) / kChunk)), dim3(kChunk), 0,
+                           st, a);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipStreamSynchronize(st));
+        return status_code(c, c->result[0]);
+    }
     const double *qd[3] = {c->d.x, c->d.y, c->d.z};
     const double *vd[3] = {c->d.vx, c->d.vy, c->d.vz};
     for (int k = 0; k < 3 && n > 0; ++k) {
@@ -1630,16 +1699,15 @@ int qsym_energy(qsym_ctx *c, double *E)
     hipStream_t st = c->stream;
     {
         Timer tm(c, P_ENERGY);
-        EnergyArgs ea{c->d, c->p.G, c->nsys};
+        EnergyArgs ea{c->d, c->p.G, c->nsys, c->result};
         hipLaunchKernelGGL(k_energy_pairs, dim3((unsigned)(c->L.e_waves / 4)), dim3(256), 0, st, ea);
         HIPCHK(c, hipGetLastError());
         hipLaunchKernelGGL(k_energy_final, dim3(c->nsys), dim3(256), 0, st, ea);
         HIPCHK(c, hipGetLastError());
     }
-    HIPCHK(c, hipMemcpyAsync(E, c->d.E, sizeof(double) * c->nsys, hipMemcpyDeviceToHost, st));
     HIPCHK(c, hipStreamSynchronize(st));
-    leave(c);
-    return sync_status(c);
+    std::memcpy(E, c->result + 1, sizeof(double) * (size_t)c->nsys);
+    return status_code(c, c->result[0]);
 }
 
 int qsym_encounters(qsym_ctx *c, int32_t *pairs, int64_t cap, int64_t *n_pairs, int32_t *set_id)

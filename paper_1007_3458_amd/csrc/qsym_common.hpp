@@ -147,7 +147,6 @@ struct Dev {
     int *e_wrec;                                // [waves] first record of each wave
     long long *sys_u0;                          // [nsys+1] first energy unit of each system
     int *sys_r0;                                // [nsys+1] first energy record of each system
-    double *E;                                  // energies per system
     float *guess;                               // learned Kepler start: weights + scalers
 };
 

@@ -170,6 +170,70 @@ __global__ __launch_bounds__(kChunk) void k_momentum(Dev d)
     chunk_momentum(d, bc, p);
 }
 
+// A state from the caller's device arrays (m, h [n], q, v [3][n]) with its
+// momentum partials, and a clear status: one launch for what eight copies, a
+// launch and a memset took.  Bound by the launch and the wait after it.
+struct LoadArgs {
+    Dev d;
+    const double *m, *h, *q, *v;
+    long long n;
+};
+
+__global__ __launch_bounds__(kChunk) void k_load_state(LoadArgs a)
+{
+    const Dev &d = a.d;
+    const int4 bc = d.bchunk[blockIdx.x];
+    const int t = threadIdx.x;
+    double p[3] = {0.0, 0.0, 0.0};
+    if (t < bc.z) {
+        const long long i = bc.y + t;
+        const double m = a.m[i], h = a.h[i];
+        double q[3], v[3];
+        for (int k = 0; k < 3; ++k) {
+            q[k] = a.q[k * a.n + i];
+            v[k] = a.v[k * a.n + i];
+        }
+        d.m[i] = m;
+        d.h[i] = h;
+        d.x[i] = q[0];
+        d.y[i] = q[1];
+        d.z[i] = q[2];
+        d.vx[i] = v[0];
+        d.vy[i] = v[1];
+        d.vz[i] = v[2];
+        for (int k = 0; k < 3; ++k) p[k] = m * v[k];
+    }
+    chunk_momentum(d, bc, p);
+    if (blockIdx.x == 0 && t == 0) d.ctr[C_STATUS] = 0ull;
+}
+
+// The state to the caller's device arrays (q, v [3][n], either may be null),
+// and the status to host memory
+struct StoreArgs {
+    Dev d;
+    double *q, *v;
+    long long n;
+    unsigned long long *status;
+};
+
+__global__ __launch_bounds__(kChunk) void k_store_state(StoreArgs a)
+{
+    const Dev &d = a.d;
+    const long long i = (long long)blockIdx.x * kChunk + threadIdx.x;
+    if (i == 0) *a.status = d.ctr[C_STATUS];
+    if (i >= a.n) return;
+    if (a.q) {
+        a.q[i] = d.x[i];
+        a.q[a.n + i] = d.y[i];
+        a.q[2 * a.n + i] = d.z[i];
+    }
+    if (a.v) {
+        a.v[i] = d.vx[i];
+        a.v[a.n + i] = d.vy[i];
+        a.v[2 * a.n + i] = d.vz[i];
+    }
+}
+
 // ------------------------------------------------------------------------
 // E_Dft(dt): Q_i += dt * P / m0 (Sec. 2, H_Dft), optionally followed by the
 // per-body quantities of the encounter search (Sec. 2.4) at the drifted
@@ -3318,6 +3382,7 @@ struct EnergyArgs {
     Dev d;
     double G;
     int nsys;
+    unsigned long long *out;   // host memory: the status, then each system's E
 };
 
 // sum over the unit's columns [c0, c1) of m_j / r for one i, every pair
@@ -3554,7 +3619,7 @@ __global__ __launch_bounds__(256) void k_energy_pairs(EnergyArgs a)
     }
 }
 
-// E of each system from its records, added in order
+// E of each system from its records, added in order, and the status
 __global__ __launch_bounds__(256) void k_energy_final(EnergyArgs a)
 {
     __shared__ double lds[256];
@@ -3567,8 +3632,11 @@ __global__ __launch_bounds__(256) void k_energy_final(EnergyArgs a)
         for (int k = 0; k < kERec; ++k) r[k] += d.erec[(long long)kERec * q + k];
 #pragma unroll
     for (int k = 0; k < kERec; ++k) r[k] = block_sum<256>(r[k], lds);
-    if (threadIdx.x == 0)
-        d.E[s] = r[0] + (r[2] * r[2] + r[3] * r[3] + r[4] * r[4]) / (2.0 * m0) - r[1] - a.G * r[5];
+    if (threadIdx.x == 0) {
+        const double E = r[0] + (r[2] * r[2] + r[3] * r[3] + r[4] * r[4]) / (2.0 * m0) - r[1] - a.G * r[5];
+        a.out[1 + s] = (unsigned long long)__double_as_longlong(E);
+        if (s == 0) a.out[0] = d.ctr[C_STATUS];
+    }
 }
 
 
