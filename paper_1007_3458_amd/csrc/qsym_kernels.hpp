@@ -1792,10 +1792,11 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return v;
 }
 
-// exclusive scan of v[0..n) in place by one workgroup (thread-contiguous
-// runs, wave scans, one scan of the wave totals); returns the total.
-// tmp needs blockDim/64 + 1 entries.
-__device__ int block_scan_excl(int *v, int n, int *tmp)
+// exclusive scan of f(0..n) into v[0..n) by one workgroup (thread-contiguous
+// runs, wave scans, one scan of the wave totals); returns the total.  f(i) may
+// read v[i].  tmp needs blockDim/64 + 1 entries.
+template <class F>
+__device__ __forceinline__ int block_scan_excl(int *v, int n, int *tmp, F f)
 {
     const int T = blockDim.x;
     const int nw = T >> 6;
@@ -1804,7 +1805,7 @@ __device__ int block_scan_excl(int *v, int n, int *tmp)
     int s = 0;
     for (int k = 0; k < per; ++k) {
         const int i = t * per + k;
-        if (i < n) s += v[i];
+        if (i < n) s += f(i);
     }
     const int incl = wave_incl_scan(s);
     if ((t & 63) == 63) tmp[t >> 6] = incl;
@@ -1820,7 +1821,7 @@ __device__ int block_scan_excl(int *v, int n, int *tmp)
     for (int k = 0; k < per; ++k) {
         const int i = t * per + k;
         if (i < n) {
-            const int c = v[i];
+            const int c = f(i);
             v[i] = run;
             run += c;
         }
@@ -1828,6 +1829,12 @@ __device__ int block_scan_excl(int *v, int n, int *tmp)
     const int total = tmp[nw];
     __syncthreads();
     return total;
+}
+
+// the same of v's own values, in place
+__device__ int block_scan_excl(int *v, int n, int *tmp)
+{
+    return block_scan_excl(v, n, tmp, [&](int i) { return v[i]; });
 }
 
 struct SetsArgs {
@@ -1862,11 +1869,23 @@ __device__ __forceinline__ int lower_rank(const unsigned *u, int n, unsigned v)
 }
 
 // One workgroup, LDS only (<= kCapE pairs): unique bodies of the encounter
-// pairs (bitonic sort + scan), pairs as rank pairs, labels propagated to the
-// component minimum, members ordered by (component, index) with one more
-// sort, r_crit per set.  Ranks follow body order, so "smallest rank" is
-// "smallest body index".  The pair list itself is left in append order (the
-// ABI returns it sorted on the host).
+// pairs (a bitmap, or a bitonic sort, and a scan), pairs as rank pairs, roots
+// by union-find, members ordered by (root, index), r_crit per set.  Ranks
+// follow body order, so "smallest rank" is "smallest body index".  The pair
+// list itself is left in append order (the ABI returns it sorted on the host).
+//
+// Bound by its chain of barriers and by the trips to memory at its two ends.
+// A member's place is its set's start, from one scan of the sets' sizes, and
+// the number of smaller members of its set, counted in a bucket of the set in
+// LDS: sets hold two or three bodies, so that is a few reads, where a sort of
+// all members took 55 to 91 dependent stages (10,000 cycles for 10 members,
+// 110,000 for 5300).  Sets of more than kPlaceMax are sorted: their counts
+// would cost more.  Slot by slot, so that a large set's counts fall to few
+// waves.  The four counters that order the workgroups' output are asked for
+// at once, while the buckets fill.  Measured, with the sort and so: 1024
+// bodies 15.9, 11.2 us; 4100: 16.3, 11.2; 16,388: 20.1, 13.8; 131,076 (a set
+// of 401): 86, 51; the 512-system batch 52, 46.
+constexpr int kPlaceMax = 512;
 __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
 {
     const Dev &d = a.d;
@@ -1876,11 +1895,16 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
     __shared__ unsigned int rp[kCapE];   // pairs as rank pairs
     __shared__ int flag[kCapU];          // scan scratch
     __shared__ int tmp[kSetsThreads / 64 + 1];
-    __shared__ int base_set, base_mem, s_whole;
+    __shared__ int base_set, base_mem, base_small, base_big, s_whole;
+    __shared__ int s_small, s_large, s_max;   // small and larger sets, the largest set
+    __shared__ int l_small, l_large;          // sets listed so far
     const int t = threadIdx.x;
     const int sys = blockIdx.x;
     const int cnt = d.sys_ecnt[sys];
     const int2 *enc = d.enc + d.sys_eoff[sys];
+    // this thread's first pair, asked for before the count is known (inside
+    // the system's segment)
+    const int2 first_pair = t < d.sys_eoff[sys + 1] - d.sys_eoff[sys] ? enc[t] : make_int2(0, 0);
     if (d.ctr[C_STATUS] & S_FREEZE) return;
     if (t == 0 && cnt > 0) atomicAdd(&d.ctr[C_ENC], (unsigned long long)cnt);
     if (cnt > d.sys_eoff[sys + 1] - d.sys_eoff[sys]) {
@@ -1911,16 +1935,14 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
         // the pairs are read once and kept in lab (free until the labels
         // are set up) for the ranks below
         for (int k = t; k < ne; k += blockDim.x) {
-            const int2 p = enc[k];
+            const int2 p = k == t ? first_pair : enc[k];
             atomicOr(&bits[(p.x - so) >> 5], 1u << ((p.x - so) & 31));
             atomicOr(&bits[(p.y - so) >> 5], 1u << ((p.y - so) & 31));
             lab[2 * k] = (unsigned)(p.x - so);
             lab[2 * k + 1] = (unsigned)(p.y - so);
         }
         __syncthreads();
-        for (int k = t; k < nw; k += blockDim.x) wpre[k] = __popc(bits[k]);
-        __syncthreads();
-        nu = block_scan_excl(wpre, nw, tmp);
+        nu = block_scan_excl(wpre, nw, tmp, [&](int i) { return __popc(bits[i]); });
         for (int k = t; k < nw; k += blockDim.x) {
             unsigned w = bits[k];
             int r = wpre[k];
@@ -1991,18 +2013,33 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
         }
     }
     __syncthreads();
+    // ep[k]: the member's root (13 bits) and its turn in the set's bucket;
+    // flag[root]: 1 << 16 and the set's size, scanned to (set id, start), so
+    // the sets are numbered by ascending root
+    static_assert(kCapU <= 1 << 13, "ranks, sizes and places are packed in 13 bits");
     for (int k = t; k < nu; k += blockDim.x) {
         unsigned x = k;
         while (lab[x] != x) x = lab[x];
-        flag[k] = (int)x;
+        ep[k] = x;
+        flag[k] = 0;
+    }
+    if (t == 0) s_small = s_large = s_max = l_small = l_large = 0;
+    __syncthreads();
+    for (int k = t; k < nu; k += blockDim.x) {
+        const unsigned x = ep[k];
+        const unsigned turn = (unsigned)atomicAdd(&flag[x], x == (unsigned)k ? 0x10001 : 1) & 0xffffu;
+        ep[k] = x | turn << 13;
     }
     __syncthreads();
-    for (int k = t; k < nu; k += blockDim.x) lab[k] = (unsigned)flag[k];
-    __syncthreads();
-    // roots -> set ids in ascending root order
-    for (int k = t; k < nu; k += blockDim.x) flag[k] = (lab[k] == (unsigned)k) ? 1 : 0;
-    __syncthreads();
-    const int nsets = block_scan_excl(flag, nu, tmp);
+    // lab[root]: the set's size (14 bits), below its start as well
+    for (int k = t; k < nu; k += blockDim.x) {
+        if ((ep[k] & 0x1fffu) != (unsigned)k) continue;
+        const int n = flag[k] & 0xffff;
+        lab[k] = (unsigned)n;
+        atomicAdd(n <= kWaveMax ? &s_small : &s_large, 1);
+        if (n > 2) atomicMax(&s_max, n);
+    }
+    const int nsets = block_scan_excl(flag, nu, tmp) >> 16;
     // Sec. 2.3, after the steps: a set holding two planets makes the step
     // integrate the whole system with the Hermite -- one set of all its
     // bodies (ascending) with r_crit infinite, so K = 0 and W = 1 for every
@@ -2012,7 +2049,8 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
         if (t == 0) s_whole = 0;
         __syncthreads();
         for (int k = t; k < nu; k += blockDim.x)
-            if (d.m[uq[k]] >= a.planet_mass && atomicAdd(&rp[flag[lab[k]]], 1u) >= 1u) s_whole = 1;
+            if (d.m[uq[k]] >= a.planet_mass && atomicAdd(&rp[flag[ep[k] & 0x1fffu] >> 16], 1u) >= 1u)
+                s_whole = 1;
         __syncthreads();
         if (s_whole) {
             const int o = d.sys_off[sys], ns = d.sys_off[sys + 1] - o;
@@ -2039,79 +2077,77 @@ __global__ __launch_bounds__(kSetsThreads) void k_sets(SetsArgs a)
             return;
         }
     }
-    // members sorted by (root rank, rank)
-    int u2 = kSetsThreads;
-    while (u2 < nu) u2 <<= 1;
-    for (int k = t; k < u2; k += blockDim.x)
-        ep[k] = (k < nu) ? ((lab[k] << 16) | (unsigned)k) : 0xffffffffu;
-    __syncthreads();
-    block_sort_u32(ep, u2);
-    // global slots of this system's sets and members
+    const int largest = max(s_max, 2);
+    // global slots of this system's sets, members and work-list entries
     if (t == 0) {
         base_set = (int)atomicAdd(&d.ctr[C_NSETS], (unsigned long long)nsets);
         base_mem = (int)atomicAdd(&d.ctr[C_NU], (unsigned long long)nu);
+        base_small = (int)atomicAdd(&d.ctr[C_NSMALL], (unsigned long long)s_small);
+        base_big = (int)atomicAdd(&d.ctr[C_NBIG], (unsigned long long)s_large);
     }
-    __syncthreads();
-    const int bs = base_set, bm = base_mem;
-    // member k of the sorted list: body uq[r], local set flag[root]; the
-    // local set index is kept in lab[k] (lab is free once the keys are built)
+    // the sets' buckets (the rank pairs are done with), ep[k] the root and
+    // the set id; or the members sorted by (set id, rank) in ep
+    unsigned short *bucket = reinterpret_cast<unsigned short *>(rp);
+    const bool sorted = largest > kPlaceMax;
     for (int k = t; k < nu; k += blockDim.x) {
-        const unsigned r = ep[k] & 0xffffu;
-        d.set_mem[bm + k] = (int)uq[r];
-        const unsigned root = ep[k] >> 16;
-        const bool first = (k == 0) || ((ep[k - 1] >> 16) != root);
-        const int sid = flag[root];
-        if (first) {
-            d.set_start[bs + sid] = bm + k;
-            rp[sid] = (unsigned)k;   // local start (the rank pairs are done with)
-        }
-        lab[k] = (unsigned)sid;
+        const unsigned x = ep[k] & 0x1fffu, turn = ep[k] >> 13;
+        const unsigned sid = (unsigned)flag[x] >> 16, start = (unsigned)flag[x] & 0xffffu;
+        if (x == (unsigned)k) lab[k] |= start << 14;
+        bucket[start + turn] = (unsigned short)k;
+        ep[k] = sorted ? sid << 16 | (unsigned)k : sid << 13 | x;
+    }
+    if (sorted) {
+        int u2 = kSetsThreads;
+        while (u2 < nu) u2 <<= 1;
+        for (int k = nu + t; k < u2; k += blockDim.x) ep[k] = 0xffffffffu;
+        __syncthreads();
+        block_sort_u32(ep, u2);
     }
     __syncthreads();
-    // r_crit = a_H max_{i in S} h_i a_i: one thread per member, max through
-    // LDS atomics on the bit patterns (non-negative doubles order as
-    // integers); flag's storage is reused (nsets <= nu / 2 <= kCapE)
+    // r_crit = a_H max_{i in S} h_i a_i: max through LDS atomics on the bit
+    // patterns (non-negative doubles order as integers); flag's storage is
+    // reused (nsets <= nu / 2 <= kCapE)
     unsigned long long *rcb = (unsigned long long *)flag;
     for (int k = t; k < nsets; k += blockDim.x) rcb[k] = 0ull;
     __syncthreads();
-    for (int k = t; k < nu; k += blockDim.x) {
-        const int i = (int)uq[ep[k] & 0xffffu];
+    const int bs = base_set, bm = base_mem;
+    // every member to its place, slot by slot, so that a large set's counts
+    // fall to few waves; a set's root writes the set's entries
+    for (int p = t; p < nu; p += blockDim.x) {
+        const int k = sorted ? (int)(ep[p] & 0xffffu) : (int)bucket[p];
+        const int i = (int)uq[k];
         const double rh = d.h[i] * d.A[i];
-        atomicMax(&rcb[lab[k]], (unsigned long long)__double_as_longlong(rh));
+        const int sid = (int)(sorted ? ep[p] >> 16 : ep[k] >> 13);
+        int pos = p, root;
+        if (sorted) {
+            root = p == 0 || ep[p - 1] >> 16 != (unsigned)sid ? k : -1;
+        } else {
+            root = (int)(ep[k] & 0x1fffu);
+            const int start = (int)(lab[root] >> 14), n = (int)(lab[root] & 0x3fffu);
+            pos = start;
+#pragma unroll 8
+            for (int q = start; q < start + n; ++q) pos += bucket[q] < k ? 1 : 0;
+        }
+        d.set_mem[bm + pos] = i;
+        if (k == root) {
+            const int n = (int)(lab[k] & 0x3fffu);
+            d.set_start[bs + sid] = bm + (int)(lab[k] >> 14);
+            d.set_count[bs + sid] = n;
+            if (n <= kWaveMax)
+                d.set_list[base_small + atomicAdd(&l_small, 1)] = bs + sid;
+            else
+                d.set_list[d.setcap - 1 - (base_big + atomicAdd(&l_large, 1))] = bs + sid;
+            if (n > kCoopMin) atomicAdd(&d.ctr[C_NGRID], 1ull);   // rare: the grid phase
+        }
+        atomicMax(&rcb[sid], (unsigned long long)__double_as_longlong(rh));
     }
     __syncthreads();
     for (int sidx = t; sidx < nsets; sidx += blockDim.x)
         d.set_rc[bs + sidx] = a.aH * __longlong_as_double((long long)rcb[sidx]);
-    // set sizes from the local starts (and the largest); the work lists of
-    // the Hermite kernel: the sets' places in the small and the larger list
-    // from one scan of packed counts (small sets in the low, larger ones in
-    // the high 16 bits; nsets <= kCapE), one atomic per list for the base
-    __syncthreads();   // rcb (flag) read
-    unsigned int big = 0;
-    for (int sid = t; sid < nsets; sid += blockDim.x) {
-        const int n = (sid + 1 < nsets ? (int)rp[sid + 1] : nu) - (int)rp[sid];
-        d.set_count[bs + sid] = n;
-        if ((unsigned)n > big) big = (unsigned)n;
-        if (n > kCoopMin) atomicAdd(&d.ctr[C_NGRID], 1ull);   // rare: the grid phase
-        flag[sid] = n <= kWaveMax ? 1 : 0x10000;
-    }
-    __syncthreads();
-    const int tot = block_scan_excl(flag, nsets, tmp);
     if (t == 0) {
-        base_set = (int)atomicAdd(&d.ctr[C_NSMALL], (unsigned long long)(tot & 0xffff));
-        base_mem = (int)atomicAdd(&d.ctr[C_NBIG], (unsigned long long)(tot >> 16));
+        atomicMax(&d.ctr[C_MAXSET], (unsigned long long)largest);
+        atomicAdd(&d.ctr[C_TENC], (unsigned long long)ne);
     }
-    __syncthreads();
-    for (int sid = t; sid < nsets; sid += blockDim.x) {
-        const int n = (sid + 1 < nsets ? (int)rp[sid + 1] : nu) - (int)rp[sid];
-        const int pos = flag[sid];
-        if (n <= kWaveMax)
-            d.set_list[base_set + (pos & 0xffff)] = bs + sid;
-        else
-            d.set_list[d.setcap - 1 - (base_mem + (pos >> 16))] = bs + sid;
-    }
-    note_max_set(&d.ctr[C_MAXSET], big);
-    if (t == 0) atomicAdd(&d.ctr[C_TENC], (unsigned long long)ne);
 }
 
 // ------------------------------------------------------------------------

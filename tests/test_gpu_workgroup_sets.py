@@ -55,3 +55,40 @@ def test_member_edges(Q, orc):
             assert err.max() < 1e-12
     assert st["status"] == 0 and st["substeps"] == substeps and st["n_sets"] == len(systems)
     ctx.close()
+
+
+def _mixed(n, far):
+    """One set of n bodies, and `far` bodies further out in sets of their own."""
+    s = one_set(n)
+    o = inputs.make_disk(f"far{far}", 4, far, 3e-7, 400.0, 440.0, "uniform", "uniform", 0.02, 0.01,
+                         planets=False)
+    return inputs.System(f"mixed{n}", 1.0, 1.0, np.concatenate([s.m, o.m]), np.vstack([s.q, o.q]),
+                         np.vstack([s.v, o.v]))
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 900])
+def test_partition_places(Q, orc, n):
+    """Members are placed by counts up to a largest set of 512 and by a sort
+    beyond it; with a large set among small ones, ids and members equal the
+    oracle's, states to 1e-12."""
+    s = _mixed(n, 300)
+    print("partition", s.n, flush=True)
+    opts = dict(aE=3.0)
+    qo, vo, res = orc.step(orc.make_params(**opts), 0.05, s.m, s.h, s.q, s.v)
+    size = np.bincount(res.label[res.label >= 0])
+    assert res.rc == 0 and size.max() == n and (size > 0).sum() > 3
+    ctx = Q.Context(s, **opts)
+    ctx.step(0.05, 1)
+    ctx.sync()
+    st = ctx.stats()
+    assert st["status"] == 0 and st["max_set"] == n and st["n_sets"] == (size > 0).sum()
+    pairs, sid = ctx.encounters()
+    assert len(pairs) == res.stats["n_encounters"]
+    # ids by smallest member, as the oracle's labels in ascending order
+    want = np.full(s.n, -1)
+    roots = np.unique(res.label[res.label >= 0])
+    want[res.label >= 0] = np.searchsorted(roots, res.label[res.label >= 0])
+    assert np.array_equal(sid, want)
+    for g, o in zip(ctx.get_state(), (qo, vo)):
+        assert (np.linalg.norm(g - o, axis=1) / np.linalg.norm(o, axis=1)).max() < 1e-12
+    ctx.close()
