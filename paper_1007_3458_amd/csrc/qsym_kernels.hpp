@@ -2621,13 +2621,17 @@ __device__ void herm_pairs(const SetLds &S, int n, int a, int l, int L, double G
     for (int c = 0; c < 3; ++c) acc[c] = jrk[c] = 0.0;
     for (int b0 = l; b0 < n; b0 += 32 * L) {
         unsigned inside = 0u;
-        for (int t = 0; t < 32; ++t) {
-            const int b = b0 + t * L;
-            if (b >= n) break;
+        // the same on every lane (L is a power of two); four at a time, their
+        // reads together: one after the other, a member waited 250 cycles
+        const int nt = min(32, (n - b0 + l + L - 1) >> __builtin_ctz(L));
+#pragma unroll 4
+        for (int t = 0; t < nt; ++t) {
+            const int b = min(b0 + t * L, n - 1);
             const double d0 = S.x[b] - X0, d1 = S.y[b] - X1, d2 = S.z[b] - X2;
             const double s2 = fma(d2, d2, fma(d1, d1, fma(d0, d0, eps2)));
             // beyond r_crit W = 0 and K'' = 0: the pair adds exactly zero
-            if (b != a && !(s2 == 0.0 || s2 >= tc.rc2)) inside |= 1u << t;
+            const bool in = b0 + t * L < n && b != a && !(s2 == 0.0 || s2 >= tc.rc2);
+            inside |= in ? 1u << t : 0u;
         }
         // dot products and sums as explicit fused multiply-adds (the
         // library contracts nothing by itself)
