@@ -9,8 +9,8 @@ sweep, sets, corrections + Hermite, second kick, drift.
 
 Prints one JSON line.  `value` is pair-interactions per second (two all-pairs
 kicks per step, N(N-1) ordered pairs each per system) over the timed steps,
-inputs resident in HBM, as the library runs them: the captured step graph
-replayed K times between two device synchronisations.  A separate profiled
+inputs resident in HBM, as the library runs them: one call of K steps
+between two device synchronisations.  A separate profiled
 pass of the same K steps (eager launches with HIP events around every kernel,
 the energy evaluated between segments outside the timed time) gives the
 per-kernel averages, the roofline's launch duration and the energy error;
@@ -475,7 +475,7 @@ def main():
         "steps_per_s_graph": gsps,
         "value_profiled": value_profiled,
         "steps_per_s_profiled": steps / T,
-        "timing": ("graph replay of the captured step" if gsps else "eager launches with HIP events")
+        "timing": ("one call of all steps" if gsps else "eager launches with HIP events")
         + "; per-kernel averages from the profiled pass",
         "higher_is_better": True,
         "scaling": "weak",
