@@ -614,15 +614,15 @@ __device__ __forceinline__ double pair_bound(const KickArgs &ka, double hi, doub
     return th * th * 1.000000000001;
 }
 
-// A tile whose hits overflowed the queue (a crowd).  A thread takes its body i at (xi, yi, zi) against the tile's
-// nj bodies from jt on again, with the pair's own threshold in place of the
-// tile's: the j side from LDS (pos(jj) and the crude terms cj, read by all
-// lanes at once), so a pair costs some 15 instructions; the few that pass
-// take the exact test.  (That test on every pair, each operand from global
-// memory, was one chain of a tile's dependent reads a thread; with the
-// planets in the tile's maxima it set the crude kick's time for small
-// systems.  Measured at 104 / 1024 / 4100 bodies: 46.7 / 57.0 / 59.5 us, with
-// split_large and this pass 19.1 / 21.6 / 30.1 us.)
+// A tile whose hits overflowed the queue (a crowd).  A thread takes its body
+// i at (xi, yi, zi) against the tile's nj bodies from jt on again, with the
+// pair's own threshold in place of the tile's: the j side from LDS (pos(jj)
+// and the crude terms cj, read by all lanes at once), so a pair costs some 15
+// instructions; the few that pass take the exact test.  (That test on every
+// pair, each operand from global memory, was one chain of a tile's dependent
+// reads a thread; with the planets in the tile's maxima it set the crude
+// kick's time for small systems.  Measured at 104 / 1024 / 4100 bodies: 46.7 /
+// 57.0 / 59.5 us, with split_large and this pass 19.1 / 21.6 / 30.1 us.)
 template <int BS, int MODE, class Pos>
 __device__ __forceinline__ void tile_exact(const KickArgs &ka, int i, double xi, double yi,
                                            double zi, int jt, int nj, const double (*cj)[BS],
@@ -1059,11 +1059,11 @@ __device__ void sym_flush(const KickArgs &ka, const int *qi, const int *qj, unsi
 // REC: the variant that writes workgroup records (profiling with records;
 // a separate instantiation, so the kernel timed otherwise carries no trace
 // of them: any extra live value changes this kernel's register
-// allocation).  The timed crude kicks are held at three waves too: two
-// registers more than three allow cost the 16,388-body step 6%.  Its occupancy is held at the plain variant's (waves per
+// allocation).  Its occupancy is held at the plain variant's (waves per
 // SIMD: 4 for the plain kick and the 128-thread, one-i crude kick, 3 for
 // the other crude kicks), so that its records show the timed kernel's
-// balance.
+// balance.  The timed crude kicks are held at three waves too: two
+// registers more than three allow cost the 16,388-body step 6%.
 template <int BS, int IPL, int MODE, int PREC>
 constexpr int kick_rec_waves()
 {
@@ -1076,8 +1076,8 @@ constexpr int kick_rec_waves()
 // operations instead of 20, and the sums are scaled once, where they are
 // stored.  Measured (fused / plain): 16,388 bodies 148 / 128 -> 145 / 126
 // us, 40,003 730 / 634 -> 649 / 595 us, 65,540 1.83 / 1.64 -> 1.68 / 1.53
-// ms, 131,076 7.56 / 6.95 -> 7.17 / 6.72 ms.  Contexts of many systems keep the products:
-// with a planet in the first tile of every short chunk the batch gained
+// ms, 131,076 7.56 / 6.95 -> 7.17 / 6.72 ms.  Contexts of many systems keep
+// the products: with a planet in the first tile of every short chunk the batch gained
 // 1.5%, and its close planet encounters amplify a changed last bit.
 template <int BS, int IPL, int MODE, int PREC, bool UNIT, bool REC = false>
 __global__ __launch_bounds__(BS)
