@@ -370,7 +370,9 @@ __global__ __launch_bounds__(kChunk) void k_drift(DriftArgs a)
 // (about 24 correct bits) refined by the binomial series of (1-e)^(-3/2)
 // with e = 1 - r^2 y0^2:  m r^-3 = m y0^3 (1 + e (3/2 + 15/8 e)), which is
 // exact to FP64 rounding since |e| < 2^-22.  r^2 is floored at 1e-200 so a
-// body's own pair (and coincident bodies) contributes exactly zero.
+// body's own pair (and coincident bodies) contributes exactly zero (G m times
+// 1e300 is finite to G m of 1.8e8, so the weights are G m itself: a mass in
+// units of a light body's would overflow first).
 //
 // FP32 pair term (PREC 1): see pair32.
 //
@@ -898,13 +900,14 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
 __device__ __forceinline__ double lane_rotate1(double v) { return dpp_f64<0x134>(v); }
 
 // FP64 pair of the symmetric kick: force on i into (ax, ay, az), reaction
-// on j into (fx, fy, fz), both in units of the system's reference mass (wj,
-// wi: the masses in that unit); keep = false drops the pair.  UNI: both
-// masses are the reference mass, so the two products with them fall away.
+// on j into (fx, fy, fz); wj, wi: G m of the two; keep = false drops the
+// pair.  UNI: both have the same G m = g, and c158, c32 come multiplied by it:
+// the correction's polynomial then gives g r^-3 y0^-3 and the two products
+// fall away (a coincident pair adds g 1e300 * 0 = 0, as it does with them).
 template <bool UNI>
 __device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, double wj, double xi,
                                            double yi, double zi, double wi, double seed,
-                                           double c158, double c32, bool keep, double &ax,
+                                           double c158, double c32, double g, bool keep, double &ax,
                                            double &ay, double &az, double &fx, double &fy,
                                            double &fz, double &r2)
 {
@@ -913,7 +916,7 @@ __device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, doub
     const double y0 = __builtin_amdgcn_rsq(r2);
     const double y2 = y0 * y0;
     const double e = fma(-r2, y2, 1.0);
-    const double w = fma(e, fma(e, c158, c32), 1.0);
+    const double w = fma(e, fma(e, c158, c32), UNI ? g : 1.0);
     double r3 = (y2 * y0) * w;
     if (!keep) r3 = 0.0;
     const double sj = UNI ? r3 : wj * r3, si = UNI ? r3 : wi * r3;
@@ -926,7 +929,8 @@ __device__ __forceinline__ void pair_sym64(double xj, double yj, double zj, doub
 }
 
 // FP32 form: r^-3 from the FP32 rsq on the FP64 r^2, widened once and
-// multiplied by the FP64 mass of either body (as pair32)
+// multiplied by the FP64 mass of either body (as pair32).  UNI: both masses
+// are the unit that the sums are scaled by, so the two products fall away.
 template <bool UNI>
 __device__ __forceinline__ void pair_sym32(double xj, double yj, double zj, double wj, double xi,
                                            double yi, double zi, double wi, bool keep, double &ax,
@@ -959,7 +963,7 @@ __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *s
                                             const double *xi, const double *yi,
                                             const double *zi, const double *wi,
                                             const double *th2, int lt0,
-                                            double seed, double c158, double c32, double *ax,
+                                            double seed, double c158, double c32, double g, double *ax,
                                             double *ay, double *az, double &fx, double &fy,
                                             double &fz, int *qi, int *qj, unsigned *qn, int ib,
                                             int jsub)
@@ -992,8 +996,8 @@ __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *s
             const bool keep = u == DG ? (k > 0 && lane + k < 64) : true;
             double r2;
             if constexpr (PREC == 0)
-                pair_sym64<UNI>(xj, yj, zj, wj, xi[u], yi[u], zi[u], wi[u], seed, c158, c32, keep,
-                                ax[u], ay[u], az[u], fx, fy, fz, r2);
+                pair_sym64<UNI>(xj, yj, zj, wj, xi[u], yi[u], zi[u], wi[u], seed, c158, c32, g,
+                                keep, ax[u], ay[u], az[u], fx, fy, fz, r2);
             else
                 pair_sym32<UNI>(xj, yj, zj, wj, xi[u], yi[u], zi[u], wi[u], keep, ax[u], ay[u],
                                 az[u], fx, fy, fz, r2);
@@ -1070,15 +1074,17 @@ constexpr int kick_rec_waves()
     return MODE == 0 ? 4 : (IPL == 1 && BS == 128 ? 4 : 3);
 }
 
-// UNIT: the kick of one system counts masses in units of its last body's (a
-// disk's planetesimals share one mass).  Where a lane group and a sub-tile
-// hold nothing else the pair needs no products with the masses, 18 FP64
-// operations instead of 20, and the sums are scaled once, where they are
-// stored.  Measured (fused / plain): 16,388 bodies 148 / 128 -> 145 / 126
-// us, 40,003 730 / 634 -> 649 / 595 us, 65,540 1.83 / 1.64 -> 1.68 / 1.53
-// ms, 131,076 7.56 / 6.95 -> 7.17 / 6.72 ms.  Contexts of many systems keep
-// the products: with a planet in the first tile of every short chunk the batch gained
-// 1.5%, and its close planet encounters amplify a changed last bit.
+// UNIT: the kick of one system looks for lane groups and sub-tiles whose
+// bodies all have the last body's mass (a disk's planetesimals share one).
+// Their pairs need no products with the masses, 18 FP64 operations instead of
+// 20: in the FP64 form G m of that mass is folded into the correction's
+// constants, in the FP32 form the masses are in its units and the sums are
+// scaled once, where they are stored.  Measured without and with (fused /
+// plain): 16,388 bodies 148 / 128 and 145 / 126 us, 40,003 730 / 634 and 649 /
+// 595 us, 65,540 1.83 / 1.64 and 1.68 / 1.53 ms, 131,076 7.56 / 6.95 and 7.17 /
+// 6.72 ms.  Contexts of many systems keep the products: with a planet in the
+// first tile of every short chunk the batch gained 1.5%, and its close planet
+// encounters amplify a changed last bit.
 template <int BS, int IPL, int MODE, int PREC, bool UNIT, bool REC = false>
 __global__ __launch_bounds__(BS)
 __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() : (MODE ? 3 : 1), 4))) void k_kick_sym(
@@ -1132,13 +1138,17 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
         cn = 0u;
     }
     unsigned qstart = 0;   // queue entries left by earlier tiles of the item (uniform)
-    // mass unit (UNIT; a massless or extremely light last body is none): w is
-    // the mass a pair carries, wscale the factor of the sums
+    // the mass that a pair carries: G m, or (FP32 form) the mass in units of
+    // the last body's, wscale the factor of the sums.  There a coincident
+    // pair's r^-3 is 1e36, so no ratio to a last body within these limits
+    // overflows; a massless or extremely light last body is no unit.
+    constexpr bool SCALED = UNIT && PREC == 1;
     const double mlast = UNIT ? d.m[so + ns - 1] : 0.0;
-    const bool has_ref = UNIT && mlast > 1e-60 && mlast < 1e60;
-    const double mref = has_ref ? mlast : 1.0;
-    const double wscale = UNIT ? ka.G * mref : 1.0;
-    auto weight = [&](double m) { return UNIT ? m / mref : ka.G * m; };
+    const bool has_ref = UNIT && (!SCALED || (mlast > 1e-60 && mlast < 1e60));
+    const double mref = SCALED && has_ref ? mlast : 1.0;
+    const double wscale = SCALED ? ka.G * mref : 1.0;
+    auto weight = [&](double m) { return SCALED ? m / mref : ka.G * m; };
+    const double wuni = SCALED ? 1.0 : ka.G * mlast;   // the weight of a uniform pair's bodies
     const double seed = ka.r2seed, c158 = ka.c158;
     // 3/2 in a vector register: the correction's inner fma would otherwise
     // take two scalar operands and cost a move per pair
@@ -1152,7 +1162,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
         double ax[IPL], ay[IPL], az[IPL], th2[IPL];
         const int lt0 = 64 * IPL * wv + lane;
         bool oku[IPL];
-        bool uni = has_ref;   // (a group with padding holds a zero mass)
+        bool uni = has_ref;   // (padding is massless)
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
             const int i = ib + lt0 + 64 * u;
@@ -1162,13 +1172,13 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
             zi[u] = oku[u] ? d.z[i] : kFar;
             const double mi = oku[u] ? d.m[i] : 0.0;
             wi[u] = weight(mi);
-            uni = uni && wi[u] == 1.0;
+            uni = uni && wi[u] == wuni;
             ax[u] = ay[u] = az[u] = 0.0;
             th2[u] = -1.0;
         }
         const int iw = ib + 64 * IPL * wv;   // first i of this wave
         const bool wave_i = 64 * IPL * wv < nib;
-        const bool wuni = UNIT && __all(uni);
+        const bool iuni = UNIT && __all(uni);
         for (int jt = max(it.j0, ib); jt < jend; jt += BS) {
             const int j = jt + tid;
             const bool okj = j < jend;
@@ -1234,15 +1244,17 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 // whole waves past the i-block's end or sub-tiles past the
                 // chunk's end have no pairs (uniform per wave)
                 auto meet = [&](auto dg, auto un) {
+                    constexpr bool UN = decltype(un)::value && !SCALED;
                     sym_subtile<MODE, PREC, IPL, decltype(dg)::value, decltype(un)::value>(
-                        pxy, pzm, lane, xi, yi, zi, wi, th2, lt0, seed, c158, c32, ax, ay, az, fx,
-                        fy, fz, qi, qj, &qn, ib, jt + 64 * sub);
+                        pxy, pzm, lane, xi, yi, zi, wi, th2, lt0, seed, UN ? wuni * c158 : c158,
+                        UN ? wuni * c32 : c32, wuni, ax, ay, az, fx, fy, fz, qi, qj, &qn, ib,
+                        jt + 64 * sub);
                 };
                 using std::integral_constant;
                 if (!wave_i || jw >= jend || rel < 0) {
                     // nothing to add
                 } else if (rel >= 64 * IPL) {
-                    if (wuni && __all(pzm[lane].y == 1.0))
+                    if (iuni && __all(pzm[lane].y == wuni))
                         meet(integral_constant<int, -1>{}, integral_constant<bool, UNIT>{});
                     else
                         meet(integral_constant<int, -1>{}, integral_constant<bool, false>{});
@@ -1290,7 +1302,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                     double sum = wpart[0][c][tid];
 #pragma unroll
                     for (int w2 = 1; w2 < NW; ++w2) sum += wpart[w2][c][tid];
-                    rj[c * ns + j] = racc[c] + (UNIT ? wscale * sum : sum);
+                    rj[c * ns + j] = racc[c] + (SCALED ? wscale * sum : sum);
                 }
             }
             if constexpr (MODE != 0) {
@@ -1338,9 +1350,9 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
         for (int u = 0; u < IPL; ++u) {
             if (oku[u]) {
                 const int il = ib + lt0 + 64 * u - so;
-                d.acc[pb + il] = UNIT ? wscale * ax[u] : ax[u];
-                d.acc[pb + ns + il] = UNIT ? wscale * ay[u] : ay[u];
-                d.acc[pb + 2 * ns + il] = UNIT ? wscale * az[u] : az[u];
+                d.acc[pb + il] = SCALED ? wscale * ax[u] : ax[u];
+                d.acc[pb + ns + il] = SCALED ? wscale * ay[u] : ay[u];
+                d.acc[pb + 2 * ns + il] = SCALED ? wscale * az[u] : az[u];
             }
         }
     }

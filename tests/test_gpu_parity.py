@@ -147,6 +147,38 @@ def test_kick_mass_unit(Q, orc, n, masses):
             ctx.close()
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("heavy", [1e-8, 1e-3])
+@pytest.mark.parametrize("last", [1e-8, 1e-12, 1e-17, 1e-20, 1e-40])
+def test_coincident_pair_beside_a_light_last_body(Q, orc, last, heavy, precision):
+    """A coincident pair adds exactly nothing however much heavier than the
+    last body its members are: r^-3 of its floored r^2 times either mass stays
+    finite.  Both members among bodies of one mass, and one of them a planet;
+    forces within the operator bar (FP32 form: that form's bar)."""
+    n = 400
+    s = inputs.make_disk("coincident", 5, n, 1e-8, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025,
+                         planets=False)
+    s.m[3], s.m[-1] = heavy, last
+    s.q[3] = s.q[n - 2]      # beside the last body's chunk
+    s.q[70] = s.q[200]       # in two groups of one mass
+    s.v[:] = 0.0
+    ref = orc.accel(s.G, s.m, s.q)
+    bar = 1e-13 if precision == 0 else 2e-6
+    for sh in (dict(ipl=1, block=128, jchunk=128, remap=0, sym=1),
+               dict(ipl=2, block=128, jchunk=256, remap=3, sym=1),
+               dict(ipl=2, block=256, jchunk=512, remap=0, sym=2),
+               dict(ipl=1, block=128, jchunk=128, remap=0, sym=16),
+               dict(ipl=1, block=128, jchunk=128, remap=0, sym=0)):
+        for crude in (0.0, 0.05):
+            say("coincident", last, heavy, precision, sh, crude)
+            ctx = Q.Context(s, precision=precision)
+            ctx.set_kick_shape(**sh)
+            ctx.apply_kick(1.0, crude_tau=crude)
+            _, a = ctx.get_state()
+            assert per_body_rel(a, ref) < bar
+            ctx.close()
+
+
 @pytest.mark.parametrize("n", [4999, 5000, 9999, 10000, 13999, 14000, 19999, 20000, 60001])
 def test_default_kick_shapes(Q, orc, n):
     """The default shapes on both sides of every line of the rule: forces of
