@@ -655,7 +655,8 @@ __device__ __forceinline__ void crude_drain(const KickArgs &ka, int i0, int ni, 
         for (unsigned e = tid; e < n; e += BS) {
             const unsigned v = qbuf[e];
             const int lt = (int)(v >> 16), u = (int)((v >> 8) & 0xffu), jj = (int)(v & 0xffu);
-            if (lt + u * BS < ni) crude_exact(ka, i0 + lt + u * BS, jt + jj);
+            // (a bound beyond kFar queues the tile's padding too)
+            if (lt + u * BS < ni && jt + jj < jend) crude_exact(ka, i0 + lt + u * BS, jt + jj);
         }
     } else {
         // queue overflow: the tile is still in LDS
@@ -1035,16 +1036,17 @@ __device__ __forceinline__ void sym_subtile(const double2 *sxy, const double2 *s
 // kCrudeQ): the exact crude test of the definition, the passing pairs
 // gathered in LDS and appended to the candidate list with one atomic for
 // the workgroup (a counter every workgroup hits once per flush, not once per
-// candidate).  Called by the whole workgroup.
+// candidate).  j from jend on is the last tile's padding, which a bound beyond
+// kFar queues too.  Called by the whole workgroup.
 template <int BS>
-__device__ void sym_flush(const KickArgs &ka, const int *qi, const int *qj, unsigned n, int2 *cl,
-                          unsigned *cn, int *cbase)
+__device__ void sym_flush(const KickArgs &ka, const int *qi, const int *qj, int jend, unsigned n,
+                          int2 *cl, unsigned *cn, int *cbase)
 {
     const Dev &d = ka.d;
     const int tid = threadIdx.x;
     for (unsigned e = tid; e < n; e += BS) {
         const int i = qi[e], j = qj[e];
-        if (j > i && crude_pass(d, d.x, d.y, d.z, ka.hill_mode, ka.aE, ka.cs, ka.tau_abs, i, j)) {
+        if (j > i && j < jend && crude_pass(d, d.x, d.y, d.z, ka.hill_mode, ka.aE, ka.cs, ka.tau_abs, i, j)) {
             const unsigned k = atomicAdd(cn, 1u);
             cl[k] = make_int2(i, j);
         }
@@ -1333,7 +1335,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 }
                 const bool last = ib + BI >= it.i0 + it.ni && jt + BS >= jend;
                 if (keep > (unsigned)kCrudeQ / 2 || (last && keep > 0)) {
-                    sym_flush<BS>(ka, qi, qj, keep, cl, &cn, &cbase);
+                    sym_flush<BS>(ka, qi, qj, jend, keep, cl, &cn, &cbase);
                     keep = 0;
                 }
                 __syncthreads();   // every thread has read qn and cn
@@ -1359,7 +1361,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
     if constexpr (MODE != 0) {
         // the last tile flushes the queue; an item whose last i-block met
         // no tile would leave pairs here
-        if (qstart > 0) sym_flush<BS>(ka, qi, qj, qstart, cl, &cn, &cbase);
+        if (qstart > 0) sym_flush<BS>(ka, qi, qj, jend, qstart, cl, &cn, &cbase);
     }
     if constexpr (REC) wg_finish(ka.rec);
 }

@@ -107,6 +107,41 @@ def test_crude_candidates_match(Q, orc, name, shape):
     ctx.close()
 
 
+def nearly_parabolic(s, i, r=1e6):
+    """Body i of s at distance r with the smallest positive 2/r - v^2 that the
+    pre-pass can form there: its semi-major axis is some 1e21."""
+    s.q[i] = [r, 0.0, 0.0]
+    v = np.sqrt(2.0 / r)
+    while 2.0 / r - v * v <= 0.0:
+        v = np.nextafter(v, 0.0)
+    s.v[i] = [0.0, v, 0.0]
+
+
+@pytest.mark.parametrize("sym", [0, 1, 16])
+@pytest.mark.parametrize("n", [65, 130, 257])
+def test_crude_candidates_beside_a_nearly_parabolic_body(Q, orc, n, sym):
+    """A body whose crude limit exceeds every distance: its pairs are all of
+    its system's and none beyond (the last tile is padded, and the next system
+    follows in memory)."""
+    systems = [inputs.scaled_disk(n - 4, 40 + k) for k in range(3)]
+    for s in systems[:2]:
+        nearly_parabolic(s, 2)
+        nearly_parabolic(s, n - 1)
+    p, tau, want = orc.make_params(), 0.05, set()
+    for k, s in enumerate(systems):
+        A, ve = orc.prepass(1.0, s.q, s.v)
+        assert k == 2 or (A[2] > 1e20 and A[n - 1] > 1e20)
+        want |= {(i + k * n, j + k * n) for i, j in orc.crude(p, tau, s.q, s.h, A, ve)}
+    assert len(want) >= 2 * (2 * n - 3)
+    for block in (128, 256):
+        say("nearly parabolic", n, sym, block)
+        ctx = Q.Context(systems)
+        ctx.set_kick_shape(1, block, 512, 0, sym=sym)
+        ctx.apply_kick(0.0, crude_tau=tau)
+        assert {tuple(x) for x in ctx.candidates()} == want
+        ctx.close()
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 193, 577])
 @pytest.mark.parametrize("masses", ["equal", "two", "last_planet", "last_massless", "last_tiny",
                                     "all_massless", "ragged"])
