@@ -164,7 +164,8 @@ int qsym_get_state(qsym_ctx *ctx, double *q, double *v, int32_t where);
  * first drift, then per step its kernels and one launch of the drift that
  * ends it and begins the next (the same additions in the same order as two).
  * Small contexts replay HIP graphs of several steps, captured once 64 steps
- * of one tau were taken.  The result does not depend on how steps are split
+ * of one tau were taken; on a stream that the caller captures the launches
+ * are recorded one by one.  The result does not depend on how steps are split
  * over calls.  A negative tau integrates backwards (used with a_E = 0). */
 int qsym_step(qsym_ctx *ctx, double tau, int64_t nsteps);
 /* nsteps encounter-free steps with the Keplerian and interaction operators

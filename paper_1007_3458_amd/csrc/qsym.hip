@@ -1416,14 +1416,19 @@ int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
     // of eight, in us: 1024 bodies 1868, 1852, 1770; 4100: 2455, 2407, 2351;
     // 16,388: 7197, 7086, 7103; 8 steps of the 512-system batch 17,580,
     // 17,530, 17,970; first interval of a context, 1024 bodies: 2459, 2080.
+    // A caller who captures the stream gets the launches: a capture cannot
+    // begin inside another, and a graph launched there is not recorded.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(c->stream, &capture));
+    const bool captured = capture != hipStreamCaptureStatusNone;
     auto &G = c->g[kind];
-    if (G.tau != tau) {
+    if (!captured && G.tau != tau) {
         G.tau = tau;
         G.seen = 0;
         G.valid = false;
     }
     const int64_t mids = nsteps - 1;
-    const bool graphs = !c->profile && c->ntot < kGraphBodies;
+    const bool graphs = !c->profile && !captured && c->ntot < kGraphBodies;
     if (graphs && !G.valid && G.seen >= kGraphAfter && mids >= kGraphSteps) {
         if (G.exec) { hipGraphExecDestroy(G.exec); G.exec = nullptr; }
         if (G.graph) { hipGraphDestroy(G.graph); G.graph = nullptr; }
@@ -1447,7 +1452,7 @@ int run_steps(qsym_ctx *c, double tau, int64_t nsteps, int kind)
         for (; mids - k >= kGraphSteps; k += kGraphSteps) HIPCHK(c, hipGraphLaunch(G.exec, c->stream));
     for (; k < mids; ++k) HIPCHK(c, mid(c, tau, c->stream));
     HIPCHK(c, last(c, tau, c->stream));
-    G.seen += nsteps;
+    if (!captured) G.seen += nsteps;
     leave(c);
     return QSYM_OK;
 }
