@@ -1327,18 +1327,18 @@ hipError_t enqueue_swapped_last(qsym_ctx *c, double tau, hipStream_t st)
     return run_drift(c, tau / 2.0, 0, 0.0, 0, st, P_DRIFT2, 1);
 }
 
-// Whether the steps run in k_small_steps: systems of at most kSmallMax bodies
-// and full-matrix kicks (whose partial sums it reproduces), the crude sweep
-// fused, no per-kernel timings asked for.  A few systems of more than 192
-// bodies are left to the step's kernels, which spread a kick over several
-// compute units: one system of 200 / 256 bodies took 60 / 78 us a step in one
-// workgroup against 70 / 72, 64 of 250 bodies 103 against 148.
+// Whether this context's systems belong in k_small_steps: their sizes say so,
+// and the crude sweep is the fused one
+bool small_context(const qsym_ctx *c)
+{
+    return c->L.small && !c->p.sweep && small_route(c->off.data(), c->nsys, c->cus);
+}
+
+// Whether the steps run there now: with full-matrix kicks (whose partial sums
+// it reproduces) and no per-kernel timings asked for
 bool small_steps(const qsym_ctx *c)
 {
-    if (!c->L.small || c->p.sweep || c->profile || c->shape[0].sym || c->shape[1].sym) return false;
-    int nmax = 0;
-    for (int s = 0; s < c->nsys; ++s) nmax = std::max(nmax, nsys_bodies(c->off, s));
-    return nmax <= 192 || c->nsys >= 16;
+    return small_context(c) && !c->profile && !c->shape[0].sym && !c->shape[1].sym;
 }
 
 hipError_t run_small(qsym_ctx *c, double tau, int64_t nsteps, int kind)

@@ -3,6 +3,7 @@
 // by workgroup barriers instead of kernel boundaries.
 #pragma once
 #include "qsym_kernels.hpp"
+#include "qsym_route.hpp"
 
 namespace qsym {
 
@@ -23,7 +24,6 @@ namespace qsym {
 // thread (two chunks of 128 over 512 threads), and no set can need the
 // Hermite's grid phase.
 // ------------------------------------------------------------------------
-constexpr int kSmallMax = 256;       // bodies of the largest system
 constexpr int kSmallThreads = 512;   // as k_hermite, whose set functions run here
 constexpr int kSmallSteps = 256;     // steps per launch
 constexpr int kSmallQ = 1024;        // queued pairs under the crude bound, and candidates kept in LDS
