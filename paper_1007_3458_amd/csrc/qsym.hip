@@ -1982,6 +1982,10 @@ int qsym_autotune(qsym_ctx *c, double tau, double *us)
     HIPCHK(c, hipEventCreate(&e1));
     const int ipls[3] = {1, 2, 4};
     const int blocks[2] = {128, 256};
+    // a symmetric kick would take a small context out of k_small_steps for
+    // the sake of one kernel (512 systems of 192 bodies: 131 us a step there,
+    // 180 in the step's kernels)
+    const bool full_only = small_context(c);
     int rc = QSYM_OK;
     for (int w = 0; w < 2; ++w) {
         const int mode = w ? 1 + c->p.hill_mode : 0;
@@ -1998,13 +2002,13 @@ int qsym_autotune(qsym_ctx *c, double tau, double *us)
                     // symmetric kick: one or two i per lane
                     const long long BI = (long long)blocks[bi] * ipls[ii];
                     const long long jcs = (jc + BI - 1) / BI * BI;
-                    if (ipls[ii] <= 2)
+                    if (ipls[ii] <= 2 && !full_only)
                         for (int sy = 1; sy <= 4; sy *= 2)
                             for (int rm = 0; rm < 4; ++rm)
                                 cand.push_back(Shape{ipls[ii], blocks[bi], jcs, rm, sy});
                 }
         // balanced rows (the j-chunk plays no part: the smallest allowed)
-        for (int bi = 0; bi < 2; ++bi)
+        for (int bi = 0; bi < 2 && !full_only; ++bi)
             for (int ii = 0; ii < 2; ++ii) {
                 const long long BI = (long long)blocks[bi] * ipls[ii];
                 const long long jcs = (c->L.jchunk_min + BI - 1) / BI * BI;

@@ -107,6 +107,20 @@ def test_forty_systems_of_most_bodies(Q, n, kw):
     both(Q, systems, [(0.05, 3)], swapped=True, **kw)
 
 
+@pytest.mark.parametrize("n,nsys", [(192, 512), (128, 1024), (104, 1)])
+def test_autotune_keeps_the_one_launch(Q, n, nsys):
+    """Full-matrix shapes only, since symmetric ones would cost the context
+    its one-launch steps."""
+    base = [inputs.batch_system(k, n) for k in range(32)]
+    ctx = Q.Context([base[k % 32] for k in range(nsys)])
+    ctx.autotune(0.05)
+    say("autotune", n, nsys, ctx.kick_shape(0), ctx.kick_shape(1))
+    assert ctx.kick_shape(0)["sym"] == 0 and ctx.kick_shape(1)["sym"] == 0
+    ctx.step(0.05, 2)
+    ctx.sync()
+    ctx.close()
+
+
 @pytest.mark.parametrize("jchunk", [128, 256, 512])
 def test_kick_chunks(Q, jchunk):
     """Full-matrix shapes of other j-chunks: the same partial sums."""
