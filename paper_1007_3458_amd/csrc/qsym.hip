@@ -1615,10 +1615,12 @@ int qsym_set_state(qsym_ctx *c, const double *m, const double *h, const double *
     const size_t B = sizeof(double) * (size_t)n;
     const Span in[4] = {{m, B}, {h, B}, {q, 3 * B}, {v, 3 * B}};
     if (n > 0 && where == QSYM_DEVICE && one_kernel_moves(c, in, 4, false)) {
-        Timer tm(c, P_MOMENTUM);
-        const LoadArgs a{c->d, m, h, q, v, n};
-        hipLaunchKernelGGL(k_load_state, dim3(nblocks_chunks(c)), dim3(kChunk), 0, st, a);
-        HIPCHK(c, hipGetLastError());
+        {
+            Timer tm(c, P_MOMENTUM);
+            const LoadArgs a{c->d, m, h, q, v, n};
+            hipLaunchKernelGGL(k_load_state, dim3(nblocks_chunks(c)), dim3(kChunk), 0, st, a);
+            HIPCHK(c, hipGetLastError());
+        }
         HIPCHK(c, hipStreamSynchronize(st));   // nothing is left for the caller's stream to wait for
         return QSYM_OK;
     }

@@ -97,6 +97,31 @@ def test_nonfinite_status_reaches_every_call(Q):
     ctx.close()
 
 
+def test_profiled_device_load_is_the_kernels_time(Q):
+    """The momentum phase of a profiled set_state holds its kernel alone, from
+    device arrays (one kernel) as by copies (the momentum kernel after them),
+    not the wait of the host that follows: both are a launch between two
+    events, so the smaller of many agree within half and 2 us."""
+    import torch
+    s = disk(1029)
+    ctx = Q.Context(s)
+    ctx.profile(True)
+    cols = [torch.tensor(np.ascontiguousarray(x), device="cuda") for x in (s.m, ctx.h, s.q.T, s.v.T)]
+    least = []
+    for shift in (0, 4):
+        dev = [raw(x, shift) for x in cols]
+        torch.cuda.synchronize()
+        at, us = [ctypes.c_void_p(b.data_ptr() + shift) for b in dev], []
+        for _ in range(40):
+            before = ctx.stats()["phase_us"][10]
+            assert Q.lib().qsym_set_state(ctx.ctx, *at, Q.QSYM_DEVICE) == 0
+            us.append(ctx.stats()["phase_us"][10] - before)
+        least.append(min(us))
+    print("momentum phase us: one kernel, copies", least, flush=True)
+    assert 0.0 < least[0] <= 1.5 * least[1] + 2.0
+    ctx.close()
+
+
 def test_energy_short_waves(Q, orc):
     """Energies whose waves hold 16 columns or a few more: systems at the
     edges of the 64- and 128-body blocks, alone and together, to 1e-13 (the
