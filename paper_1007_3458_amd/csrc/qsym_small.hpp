@@ -86,9 +86,9 @@ struct SmallLds {
     unsigned long long inenc[kSmallMax / 64], root[kSmallMax / 64];
     int planets[kSmallMax / 2 + 1];
     int whole, nsets, nu, maxset, sub, hfail;
-    // Hermite staging
-    double hx[kHermLds], hy[kHermLds], hz[kHermLds], hu[kHermLds], hv[kHermLds], hw[kHermLds],
-        hm[kHermLds], hpad[kHermLds];   // (hpad: the kick's tile, 8 kHermLds doubles from hx on)
+    // Hermite staging (x, y, z, u, v, w, m); between the sets the kick's tile
+    // and, at the end, the waves' shares of the figures: one array for all
+    double stage[8][kHermLds];
     double hr[6 * kCoopMin];
     double red[kHermThreads / 64 + 1];
     unsigned hist[kHist];
@@ -159,8 +159,8 @@ __device__ __forceinline__ void small_kick_tiles(SmallLds &L, const KickArgs &ka
                 }
         }
     }
-    double *const ms = L.hx + i;   // [T][NB] over the Hermite's staging
-    static_assert(sizeof(L.hx) * 8 >= 4096 * sizeof(double), "the tile fits the staging");
+    double *const ms = &L.stage[0][0] + i;   // [T][NB] over the Hermite's staging
+    static_assert(sizeof(L.stage) >= T * NB * sizeof(double), "the tile fits the staging");
     // components of this thread in the second phase
     constexpr bool three = NG >= 3;
     const int c0 = three ? g : (g == 0 ? 0 : 2);
@@ -490,7 +490,9 @@ __device__ __forceinline__ void small_hermite(SmallLds &L, const SmallArgs &a, d
         if (__builtin_amdgcn_readfirstlane(L.scount[s]) <= kWaveMax) continue;
         int nsub, fail;
         hermite_set_block(a.h, hs, set_of(s),
-                          SetLds{L.hx, L.hy, L.hz, L.hu, L.hv, L.hw, L.hm, L.hr}, L.red, nsub, fail);
+                          SetLds{L.stage[0], L.stage[1], L.stage[2], L.stage[3], L.stage[4],
+                                 L.stage[5], L.stage[6], L.hr},
+                          L.red, nsub, fail);
         nsub_b += nsub;
         fail_b |= fail;
     }
@@ -499,9 +501,9 @@ __device__ __forceinline__ void small_hermite(SmallLds &L, const SmallArgs &a, d
         L.hfail = fail_b;
     }
     __syncthreads();
-    const SetLds S = {L.hx + w * kWaveMax, L.hy + w * kWaveMax, L.hz + w * kWaveMax,
-                      L.hu + w * kWaveMax, L.hv + w * kWaveMax, L.hw + w * kWaveMax,
-                      L.hm + w * kWaveMax};
+    const int o = w * kWaveMax;
+    const SetLds S = {L.stage[0] + o, L.stage[1] + o, L.stage[2] + o, L.stage[3] + o,
+                      L.stage[4] + o, L.stage[5] + o, L.stage[6] + o};
     int nsub_w = 0, fail_w = 0, rank = 0;
     for (int s = 0; s < nsets; ++s) {
         if (__builtin_amdgcn_readfirstlane(L.scount[s]) > kWaveMax) continue;
@@ -832,7 +834,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_steps(SmallArgs a)
     const int done = froze ? k : a.nsteps;   // (redo: every system stopped in the same step)
     // the figures of the systems: wave w those of every eighth system, one
     // per lane, then the waves' shares through LDS (the Hermite's staging)
-    unsigned long long *const share = reinterpret_cast<unsigned long long *>(L.hx);
+    unsigned long long *const share = reinterpret_cast<unsigned long long *>(L.stage[0]);
     static_assert(SS_COUNT <= 64 && kSmallThreads <= kHermLds, "a lane per figure, a word per thread");
     {
         unsigned long long v = 0;
