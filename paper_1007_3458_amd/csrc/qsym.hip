@@ -1165,6 +1165,14 @@ hipError_t enqueue_step_last(qsym_ctx *c, double tau, hipStream_t st)
 // against 29.5 / 23.7 (so the line is at 5000), 8200 53 / 47 against 76 / 64,
 // 12,000 94 / 81 against 135 / 114, 25,000 281 / 252 against 528 / 458, 40,003
 // 649 / 595 against 1293 / 1091, 90,000 3353 / 3014 against 6186 / 5502.
+// Both kicks with their reductions on either side of the lines between the
+// blocks, us of 128 / 256 / 512 i: 5200 bodies 87 / 92 / 180, 8200 119 / 132 /
+// 180, 8500 148 / 134 / 182, 9999 175 / 165 / 185, 16,000 346 / 277 / 263, 18,000
+// 463 / 340 / 349, 19,999 529 / 400 / 435, 20,500 537 / 448 / 444, 22,500 744 / 493
+// / 453.  (The 256 i as 128 threads with two each: within 5% either way from
+// 12,000 to 20,000, 277 / 281 and 340 / 358 at 16,000 and 18,000.)
+// From 532,481 bodies on i-ranges of eight blocks need more partial slots than
+// there are: the full matrix, as before the rule.
 //
 // Otherwise the full matrix, one i per lane, with j-chunks that give the
 // grid 4096 workgroups where the size allows: small kicks are bound by the
@@ -1176,8 +1184,8 @@ Shape default_shape(qsym_ctx *c)
     const long long jmin = c->L.jchunk_min;
     const long long n = c->ntot;
     if (c->nsys == 1 && n >= 5000) {
-        sh.block = n < 10000 ? 128 : (n < 14000 ? 256 : (n < 20000 ? 128 : 256));
-        sh.ipl = n < 14000 ? 1 : 2;
+        sh.block = n < 8400 ? 128 : 256;
+        sh.ipl = n < 20000 ? 1 : 2;
         sh.remap = 3;
         const long long BI = (long long)sh.block * sh.ipl;
         const long long want = std::min<long long>(n * n / (3000 * BI), 1536);

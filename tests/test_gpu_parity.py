@@ -237,6 +237,19 @@ def test_default_kick_shapes(Q, orc, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,block,ipl", [(8399, 128, 1), (8400, 256, 1), (19999, 256, 1),
+                                         (20000, 256, 2)])
+def test_default_kick_shape_lines(Q, orc, n, block, ipl):
+    """The default blocks on both sides of the rule's lines, and the forces
+    and a step with each."""
+    ctx = Q.Context(inputs.scaled_disk(n - 4, 6), shapes=None)
+    for w in (0, 1):
+        sh = ctx.kick_shape(w)
+        assert (sh["block"], sh["ipl"], sh["remap"], sh["sym"]) == (block, ipl, 3, 1)
+    ctx.close()
+    test_default_kick_shapes(Q, orc, n)
+
+
 def _planets_among(n, at, seed, m=1e-8):
     """A disk of n bodies whose four planets stand at body indices ``at``."""
     s = inputs.make_disk(f"among{n}", seed, n - 4, m, 15.0, 40.0, "rayleigh", "rayleigh", 0.05, 0.025)
