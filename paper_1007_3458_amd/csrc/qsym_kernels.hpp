@@ -900,6 +900,16 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1, 4))) void
 // lane 0)
 __device__ __forceinline__ double lane_rotate1(double v) { return dpp_f64<0x134>(v); }
 
+// a value equal on all lanes (a wave reduction) moved to scalar registers,
+// so the loops and branches that test it are uniform to the compiler too
+__device__ __forceinline__ double wave_uniform(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // FP64 pair of the symmetric kick: force on i into (ax, ay, az), reaction
 // on j into (fx, fy, fz); wj, wi: G m of the two; keep = false drops the
 // pair.  UNI: both have the same G m = g, and c158, c32 come multiplied by it:
@@ -1150,7 +1160,9 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
     const double mref = SCALED && has_ref ? mlast : 1.0;
     const double wscale = SCALED ? ka.G * mref : 1.0;
     auto weight = [&](double m) { return SCALED ? m / mref : ka.G * m; };
-    const double wuni = SCALED ? 1.0 : ka.G * mlast;   // the weight of a uniform pair's bodies
+    // the weight of a uniform pair's bodies, in scalar registers
+    const double wuni = SCALED ? 1.0 : wave_uniform(ka.G * mlast);
+    const double gc158 = wave_uniform(wuni * ka.c158);
     const double seed = ka.r2seed, c158 = ka.c158;
     // 3/2 in a vector register: the correction's inner fma would otherwise
     // take two scalar operands and cost a move per pair
@@ -1248,7 +1260,7 @@ __attribute__((amdgpu_waves_per_eu(REC ? kick_rec_waves<BS, IPL, MODE, PREC>() :
                 auto meet = [&](auto dg, auto un) {
                     constexpr bool UN = decltype(un)::value && !SCALED;
                     sym_subtile<MODE, PREC, IPL, decltype(dg)::value, decltype(un)::value>(
-                        pxy, pzm, lane, xi, yi, zi, wi, th2, lt0, seed, UN ? wuni * c158 : c158,
+                        pxy, pzm, lane, xi, yi, zi, wi, th2, lt0, seed, UN ? gc158 : c158,
                         UN ? wuni * c32 : c32, wuni, ax, ay, az, fx, fy, fz, qi, qj, &qn, ib,
                         jt + 64 * sub);
                 };
@@ -2760,16 +2772,6 @@ __device__ __forceinline__ double wave_min(double v)
     v = fmin(v, group_partner<3>(v));
     return fmin(fmin(readlane_f64(v, 0), readlane_f64(v, 16)),
                 fmin(readlane_f64(v, 32), readlane_f64(v, 48)));
-}
-
-// a value equal on all lanes (a wave reduction) moved to scalar registers,
-// so the loops and branches that test it are uniform to the compiler too
-__device__ __forceinline__ double wave_uniform(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // One set of at most kWaveMax members on one wave: member k on lanes
