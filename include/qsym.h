@@ -159,10 +159,14 @@ int qsym_set_state(qsym_ctx *ctx, const double *m, const double *h, const double
                    const double *v, int32_t where);
 int qsym_get_state(qsym_ctx *ctx, double *q, double *v, int32_t where);
 
-/* nsteps hybrid steps of size tau (Sec. 2.3).  Asynchronous.  Systems of at
- * most 256 bodies take up to 256 steps in one launch; otherwise a call is the
+/* nsteps hybrid steps of size tau (Sec. 2.3).  Asynchronous.  A context of
+ * small systems (none above 200 bodies, or none above 256 and 40 or more
+ * above 200; not thousands of systems that average 32 bodies or fewer) takes up
+ * to 256 steps in one launch, with full-matrix kick shapes (the default
+ * there), the fused sweep and profiling off; otherwise a call is the
  * first drift, then per step its kernels and one launch of the drift that
  * ends it and begins the next (the same additions in the same order as two).
+ * Both ways give the same bits.
  * Small contexts replay HIP graphs of several steps, captured once 64 steps
  * of one tau were taken; on a stream that the caller captures the launches
  * are recorded one by one.  The result does not depend on how steps are split
@@ -263,7 +267,9 @@ int qsym_get_kick_shape(qsym_ctx *ctx, int32_t which, int32_t *ipl, int32_t *blo
                         int64_t *jchunk, int32_t *remap, int32_t *sym);
 int qsym_autotune(qsym_ctx *ctx, double tau, double *us);
 
-/* Profiling: when enabled, qsym_step launches kernels directly (no graph)
+/* Profiling: when enabled, qsym_step launches kernels directly (no graph,
+ * and no single launch for the steps of small systems, whose phases are then
+ * those of kernels that they do not run with it off)
  * with HIP events around each launch, accumulating per-kernel time into
  * qsym_stats_t.phase_us.  Kernel index order: 0 drift+prepass, 1 kick with
  * crude sweep, 2 kick apply + Kepler, 3 fine sweep, 4 sets, 5 Hermite,

@@ -14,11 +14,14 @@ namespace qsym {
 // latency of the chains of one step: at 104 bodies 86k cycles, of them 38k
 // in the two kicks, 21k in Kepler's equation (the slowest body's iterations),
 // 12k in a two-body set's Hermite.  Measured per step, in us, the step's own
-// kernels and this: 8 systems of four planets 50 and 11.6, one of 104 bodies
-// 71 and 37.6, 64 of 100 bodies 96 and 43, 512 of 250 bodies 399 and 197.
-// The arithmetic, its order and its results are those of the step's kernels over full-matrix kick shapes bit
-// for bit: the same device functions, partial sums over the same j-chunks
-// added in the same order, the momentum over the same 64-body chunks.
+// kernels and this: 8 systems of four planets 46 and 19, 16 of 100 bodies 71
+// and 40, 256 of 100 102 and 41, 512 of 250 bodies 190 and 165.  Which contexts
+// take it: small_route.
+//
+// The arithmetic, its order and its results are those of the step's kernels
+// over full-matrix kick shapes bit for bit: the same device functions,
+// partial sums over the same j-chunks added in the same order, the momentum
+// over the same 64-body chunks.
 //
 // Up to kSmallMax bodies a system: a kick then is at most 128 pair terms a
 // thread (two chunks of 128 over 512 threads), and no set can need the
