@@ -160,8 +160,8 @@ int qsym_set_state(qsym_ctx *ctx, const double *m, const double *h, const double
 int qsym_get_state(qsym_ctx *ctx, double *q, double *v, int32_t where);
 
 /* nsteps hybrid steps of size tau (Sec. 2.3).  Asynchronous.  A context of
- * small systems (none above 200 bodies, or none above 256 and 40 or more
- * above 200; not thousands of systems that average 32 bodies or fewer) takes up
+ * small systems (none above 192 bodies, or none above 256 and many of them;
+ * not thousands of systems that average 32 bodies or fewer) takes up
  * to 256 steps in one launch, with full-matrix kick shapes (the default
  * there), the fused sweep and profiling off; otherwise a call is the
  * first drift, then per step its kernels and one launch of the drift that

@@ -33,16 +33,17 @@ def route(tmp_path_factory):
 
 
 @pytest.mark.parametrize("sizes,want", [
-    ([1], True), ([200], True), ([201], False), ([256], False), ([257], False),
-    ([200] * 39, True), ([201] * 39, False), ([201] * 40, True), ([256] * 40, True),
-    # one system that is large for one compute unit decides, not how many there are
-    ([256] + [4] * 15, False), ([256] + [4] * 1000, False), ([0, 256, 0] + [100] * 60, False),
-    ([256] * 40 + [257], False), ([256] * 40 + [4] * 15, True),
-    ([4] * 1280, True), ([4] * 1281, False), ([32] * 1281, False), ([33] * 1281, True),
-    ([0] * 5000, False), ([0] * 16, True), ([200] * 4096, True)])
+    ([1], True), ([192], True), ([193], False), ([256], False), ([257], False),
+    ([192] * 39, True), ([200] * 4, False), ([200] * 5, True), ([225] * 20, False), ([225] * 21, True),
+    ([256] * 44, False), ([256] * 45, True),
+    # one large system among tiny ones: the work decides, not how many there are
+    ([256] + [4] * 15, False), ([256] + [4] * 63, False), ([0, 256, 0] + [100] * 60, False),
+    ([256] + [100] * 100, True), ([256] * 60 + [257], False), ([256] * 60 + [4] * 15, True),
+    ([4] * 1536, True), ([4] * 1537, False), ([32] * 1537, False), ([33] * 1537, True),
+    ([0] * 5000, False), ([0] * 16, True), ([192] * 4096, True)])
 def test_lines_of_the_rule(route, sizes, want):
     assert route(sizes) == want
 
 
 def test_rounds_follow_the_device(route):
-    assert route([4] * 320, 64) and not route([4] * 321, 64)
+    assert route([4] * 384, 64) and not route([4] * 385, 64)
